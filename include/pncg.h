@@ -313,7 +313,8 @@ int pncg_step_dev(pncg_ctx* ctx, const double* x_dev, const double* v_dev,
  * scratch (its status record, the per-block partial sums of the
  * per-iteration kernels and one scalar record per iteration) lives in a
  * static device array of 1 MiB that the library holds on every device it
- * runs on until the process ends; the per-vertex state and the candidate
+ * runs on until the process ends; the per-vertex state, the tables and
+ * exchange buffers of the persistent iteration kernel and the candidate
  * buffers are the context's, sized by pncg_set_mesh, pncg_set_contact and
  * earlier steps.  Every call on one device shares that device's array, so
  * calls that overlap on one device (from two host threads, or on two
@@ -386,7 +387,9 @@ int pncg_min_distance(pncg_ctx* ctx, const double* x, double* dmin,
 
 /* Per-kernel timing of steps (tracing aid).  With profiling on, every
  * launch a step makes is bracketed by HIP events recorded on the context's
- * stream; durations are summed per kind:
+ * stream, and the iterations are launched one by one (otherwise one launch
+ * runs many of them where the mesh and the contact allow; the results are the
+ * same bits); durations are summed per kind:
  *   PNCG_PROF_NARROW  first launch of an iteration with self contact
  *                     under the atomic scatter or with
  *                     PNCG_SPLIT_OBJECTS (update + pair gradient/diagonal)

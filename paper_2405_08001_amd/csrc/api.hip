@@ -16,13 +16,16 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/pncg.h"
 #include "adjoint.h"
 #include "host_mesh.h"
 #include "internal.h"
+#include "iteration_common.h"
 #include "kernels.h"
+#include "persist.h"
 
 using namespace pncg;
 
@@ -64,6 +67,37 @@ hipError_t scratch_address(int device, void** out) {
   *out = g_scratch_ptr[device];
   return hipSuccess;
 }
+
+// Compute units that persistent iteration launches of this process hold on
+// each device.  Such a launch needs all its blocks (at most one per compute
+// unit) resident at once, so launches whose blocks add up to no more than the
+// device's compute units can overlap; one that would not fit beside those in
+// flight uses the per-iteration launches instead (same bits).
+std::mutex g_units_mu;
+int g_units_used[kMaxDevices] = {0};
+
+struct UnitsHeld {
+  int device = 0, n = 0;
+  ~UnitsHeld() { release(); }
+  bool acquire(int dev, int blocks, int units) {
+    std::lock_guard<std::mutex> lock(g_units_mu);
+    if (dev < 0 || dev >= kMaxDevices || g_units_used[dev] + blocks > units) return false;
+    g_units_used[dev] += blocks;
+    device = dev;
+    n = blocks;
+    return true;
+  }
+  void release() {
+    if (!n) return;
+    std::lock_guard<std::mutex> lock(g_units_mu);
+    g_units_used[device] -= n;
+    n = 0;
+  }
+};
+
+#ifndef PNCG_PERSIST_WAIT
+#define PNCG_PERSIST_WAIT 2000000   // longest wait of a meeting, in ticks of the 100 MHz clock (20 ms)
+#endif
 
 struct DevBuf {
   void* p = nullptr;
@@ -177,6 +211,12 @@ struct pncg_ctx {
   long long *d_part_cnt = nullptr, *d_part_off = nullptr, *d_totals = nullptr;
   long long work_cap = 0;
   int grid = 1;
+  // persistent iteration kernel: tables and exchange buffers (set_mesh)
+  bool persist_ok = false;      // the mesh has tables
+  int persist_off = 0;          // after a timed-out meeting: steps that still use the per-iteration launches
+  signed char persist_fit[3][2] = {{-1, -1}, {-1, -1}, {-1, -1}};   // by [model][self]: kernel fits (-1 not asked yet)
+  int units = 0;                // compute units of the device
+  PersistArgs persist{};
   // adjoint (allocated on first use)
   bool adj_ready = false;
   bool adj_warm = false;       // start each adjoint CG from the previous call's lambda
@@ -267,6 +307,7 @@ int ensure_device(pncg_ctx* c) {
   if (c->device < 0 || c->device >= n) return fail(c, PNCG_E_INVAL, "device ordinal out of range");
   HIPCHK(c, hipSetDevice(c->device));
   HIPCHK(c, scratch_address(c->device, &c->d_static));
+  HIPCHK(c, hipDeviceGetAttribute(&c->units, hipDeviceAttributeMultiprocessorCount, c->device));
   if (!c->stream) {
     HIPCHK(c, hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking));
     c->own_stream = true;
@@ -553,6 +594,8 @@ int build_candidates(pncg_ctx* c, const double4* x, double r, double filter_d, i
 }
 
 constexpr int kRestart = 1000;   // internal: a capacity was exceeded, run the step again
+constexpr int kRestartLaunches = 1001;   // internal: a meeting of the persistent kernel timed out, run the step again
+constexpr int kPersistBackoff = 64;      // steps without the persistent kernel after that
 
 // The solver's candidate list at device positions x (pairs within
 // dhat + skin, unordered, kind in the pair), built without host
@@ -693,6 +736,19 @@ int read_status(pncg_ctx* c) {
 }
 
 // ------------------------------------------------------------------ step
+// Whether the step's iterations can run in the persistent kernel.
+template <typename R>
+bool persist_usable(pncg_ctx* c, const Args<R>& A) {
+  if (!c->persist_ok || c->profiling || A.split || (A.self && !A.seg)) return false;
+  if (c->persist_off > 0) return false;
+  signed char& fit = c->persist_fit[A.model][A.self];
+  if (fit < 0) {
+    bool ok = false;
+    fit = persist_fits<R>(c->persist, A.model, A.self != 0, c->units, &ok) == hipSuccess && ok ? 1 : 0;
+  }
+  return fit == 1;
+}
+
 // sync_end = false (the steps of pncg_run_dev but its last): the step ends as
 // soon as a chunk's status shows the stop, with the output kernel queued and
 // no further host wait, so that the next step's launches follow at once; its
@@ -752,11 +808,28 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
   // supersedes it if the step resumes.
   const bool early_final = true;
   bool last_is_final = false;
+  // The persistent kernel takes the iterations where it can: one step size,
+  // no per-launch timing, and no contact or sparse contact by the segmented
+  // scatter (dense contact needs the evenly split pair pass of k_narrow).
+  const bool may_persist = persist_usable<R>(c, A);
+  bool persist_now = false;
+  UnitsHeld held;
   auto launch_chunk = [&](int k0, int m, int mode0) {
     // fold the pair pass into the sweep while the last list had at most one
     // corner entry per vertex on average (sparse contact)
     A.fuse = 4 * c->last_ncand <= (long long)c->nV ? 1 : 0;
     const bool fused = fused_pairs(A);
+    // (it starts from a complete x_k: at the step's beginning, after a pause
+    // or where it left off, not behind a chunk of launches)
+    persist_now = may_persist && (k0 == 0 || mode0 != kModeNormal) && (!A.self || fused) &&
+                  held.acquire(c->device, c->persist.blocks, c->units);
+    if (persist_now) {
+      launch_persist<R>(A, c->persist, k0, mode0, c->stream);
+      launch_finalize<R>(A, x_out, v_out, c->stream);   // writes only if the step has stopped
+      last_is_final = true;
+      return std::min(k0 + kPersistMaxIters, c->iter_max + 1);
+    }
+    if (mode0 == kModeContinue) mode0 = kModeResume;   // x_k and its scalars are complete either way
     const int kind_first = (A.self && !fused) ? PNCG_PROF_NARROW : PNCG_PROF_GRAD;
     const int kend = std::min(k0 + m, c->iter_max + 1);
     last_is_final = false;
@@ -804,15 +877,17 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
   if ((rc = enqueue_status(c, cur))) return rc;
   while (true) {
     int kn = -1;
-    if (ahead && kend <= c->iter_max) {
+    if (ahead && !persist_now && kend <= c->iter_max) {
       kn = launch_chunk(kend, chunk_len(D + rate * (kend - k)), 0);
       if ((rc = enqueue_status(c, cur ^ 1))) return bail(rc);
     }
     if ((rc = wait_status(c, cur))) return bail(rc);
     const StepStatus s = c->h_status[cur];
     last_s = s;
+    held.release();
     if (A.self) c->last_ncand = s.n_cand;
     if (s.err & kErrCapacity) return bail(kRestart);
+    if (s.err & kErrSync) return bail(kRestartLaunches);
     if ((rc = check_status_err(c, s))) return bail(rc);
     if (s.stopped) break;
     if (s.paused_at >= 0) {
@@ -837,7 +912,7 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
       kend = kn;
       cur ^= 1;
     } else {
-      kend = launch_chunk(k, chunk_len(D), 0);
+      kend = launch_chunk(k, chunk_len(D), persist_now ? kModeContinue : 0);
       if ((rc = enqueue_status(c, cur))) return bail(rc);
     }
   }
@@ -847,7 +922,8 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
     prof_end(c, ev);
   }
   StepStatus s = last_s;
-  if (sync_end) {
+  if (sync_end && !last_is_final) {
+    // (behind an output kernel, the status in hand is already the final one)
     if ((rc = read_status(c))) return rc;
     s = *c->h_status;
     if ((rc = check_status_err(c, s))) return rc;
@@ -1108,6 +1184,43 @@ int grid_for(const pncg_ctx* c) {
 
 }  // namespace
 
+// Tables and exchange buffers of the persistent iteration kernel for the mesh
+// just committed (none if a block's share does not fit in LDS).
+static int setup_persist(pncg_ctx* c) {
+  c->persist_ok = false;
+  c->persist_off = 0;
+  for (auto& m : c->persist_fit) m[0] = m[1] = -1;
+  PersistTables T;
+  PersistArgs& P = c->persist;
+  const bool fp64 = c->precision == PNCG_FP64;
+  if (!persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, fp64, c->nF + c->nE > 0, T, P))
+    return PNCG_OK;
+  std::vector<uint8_t> fl(c->vflag);
+  for (int i : c->tris) fl[i] |= kPairVertex;
+  for (int i : c->edges) fl[i] |= kPairVertex;
+  int rc;
+  auto put = [&](auto& vec, auto*& dst) -> int {
+    using T_ = typename std::remove_reference<decltype(vec)>::type::value_type;
+    T_* d = nullptr;
+    int r = dmalloc(c, &d, vec.size());
+    if (r) return r;
+    dst = d;
+    HIPCHK(c, hipMemcpyAsync(d, vec.data(), sizeof(T_) * vec.size(), hipMemcpyHostToDevice, c->stream));
+    return PNCG_OK;
+  };
+  if ((rc = put(T.blk, P.blk)) || (rc = put(T.loc_v, P.loc_v)) || (rc = put(T.tet_e, P.tet_e)) ||
+      (rc = put(T.tet_l, P.tet_l)) || (rc = put(T.lane, P.lane)) || (rc = put(T.dtet, P.dtet)) ||
+      (rc = put(T.dvert, P.dvert)) || (rc = put(fl, P.lflag)))
+    return rc;
+  if ((rc = dmalloc(c, &P.slot_grad, 24 * (size_t)P.grid)) || (rc = dmalloc(c, &P.slot_dir, 9 * (size_t)P.grid)) ||
+      (rc = dmalloc(c, &P.pgx, 9 * (size_t)c->nV)) || (rc = dmalloc(c, &P.ring, 1)))
+    return rc;
+  P.limit = PNCG_PERSIST_WAIT;
+  persist_clear(P, c->nV, c->stream);
+  c->persist_ok = true;
+  return sync(c);
+}
+
 // =================================================================== C ABI
 // Objects of the split step must be contiguous vertex ranges (non-decreasing
 // ids) whose tets are contiguous too; the reason if not, else NULL.
@@ -1291,6 +1404,7 @@ int pncg_set_mesh(pncg_ctx* c, int32_t nV, const double* X, int32_t nT, const in
     HIPCHK(c, hipMemsetAsync(c->d_wrange, 0, sizeof(int2) * wv.size(), c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
   }
+  if ((rc = setup_persist(c))) return rc;
   c->scal_cap = 0;
   c->d_scal = nullptr;
   c->split_ready = false;
@@ -1597,6 +1711,14 @@ static int ensure_scal(pncg_ctx* c) {
   return PNCG_OK;
 }
 
+// After a meeting of the persistent kernel timed out (its blocks were not all
+// resident: another process holds part of the device): empty the exchange
+// buffers and leave the kernel out for a while.
+static void restart_launches(pncg_ctx* c) {
+  persist_clear(c->persist, c->nV, c->stream);
+  c->persist_off = kPersistBackoff;
+}
+
 static int step_dev(pncg_ctx* c, const double* x, const double* v, double h, double* x_out, double* v_out,
                     pncg_stats* st, bool sync_end) {
   int rc = ready(c);
@@ -1609,6 +1731,12 @@ static int step_dev(pncg_ctx* c, const double* x, const double* v, double h, dou
     if (st) std::memset(st, 0, sizeof(*st));
     rc = c->precision == PNCG_MIXED ? step_impl<float>(c, x, v, h, x_out, v_out, st, sync_end)
                                     : step_impl<double>(c, x, v, h, x_out, v_out, st, sync_end);
+    if (rc == kRestartLaunches) {
+      restart_launches(c);
+      --attempt;   // at most once per step: persist_off keeps the rerun on the per-iteration launches
+      continue;
+    }
+    if (c->persist_off > 0 && rc != kRestart) --c->persist_off;
     if (rc != kRestart) return rc;
     if ((rc = grow_solver_buffers(c))) return rc;
   }
@@ -1647,8 +1775,13 @@ int pncg_step_dev_noalloc(pncg_ctx* c, const double* x, const double* v, double 
   c->scal_cap = kScratchScalRecords;
   c->noalloc = true;
   if (st) std::memset(st, 0, sizeof(*st));
-  rc = c->precision == PNCG_MIXED ? step_impl<float>(c, x, v, h, x_out, v_out, st)
-                                  : step_impl<double>(c, x, v, h, x_out, v_out, st);
+  for (int attempt = 0; attempt < 2; ++attempt) {
+    rc = c->precision == PNCG_MIXED ? step_impl<float>(c, x, v, h, x_out, v_out, st)
+                                    : step_impl<double>(c, x, v, h, x_out, v_out, st);
+    if (rc != kRestartLaunches) break;
+    restart_launches(c);
+  }
+  if (c->persist_off > 0) --c->persist_off;
   c->noalloc = false;
   c->d_status = status;
   c->d_part_grad = pg;

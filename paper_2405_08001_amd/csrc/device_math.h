@@ -213,7 +213,8 @@ __device__ __forceinline__ void i23_grad_diag(const Kin<R>& k, R a2, R vpsi3, R 
   V3<R> Fb = ba.x * k.f[0] + ba.y * k.f[1] + ba.z * k.f[2];
   V3<R> Cb = ba.x * k.c[0] + ba.y * k.c[1] + ba.z * k.c[2];
   g = a2 * Fb + vpsi3 * Cb;
-  R bb = a2 * dot(ba, ba);
+  // (the fused order spelled out, so that every kernel rounds it alike)
+  R bb = a2 * std::fma(ba.z, ba.z, std::fma(ba.x, ba.x, ba.y * ba.y));
   dg = mk3(bb + vpsi33 * Cb.x * Cb.x, bb + vpsi33 * Cb.y * Cb.y, bb + vpsi33 * Cb.z * Cb.z);
 }
 

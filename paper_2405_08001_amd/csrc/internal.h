@@ -26,6 +26,7 @@ constexpr int kErrPenetration = 2;
 constexpr int kErrNonfinite = 4;
 constexpr int kErrCapacity = 8;
 constexpr int kErrTeam = 16;       // a team barrier of the batched kernel timed out
+constexpr int kErrSync = 32;       // a meeting of the persistent iteration kernel timed out
 
 // beta of iteration k > 0 by the rule in bits 4..6 of the solver flags, from
 // this iteration's g^T P g, g^T P y, y^T d, y^T P y, d^T g and the previous
