@@ -1175,6 +1175,17 @@ double default_skin(double dhat, double lmean) {
   return std::min(8.0 * dhat, std::max(2.0 * dhat, 0.4 * lmean - dhat));
 }
 
+// Cell of the broad phase's grid: 1.5 x the mean rest length of the surface
+// edges, and at least the candidate inflation, so that a primitive's box
+// touches a few cells and a cell holds a few primitives.  A caller's cell is
+// used where it is larger; the candidate lists do not depend on the cell, and
+// a finer one only multiplies the entries: the 15,360-tet bar with 1 cm edges
+// and a 2 mm cell put each edge into some 300 cells, and a rebuild took
+// 1.17 ms (k_emit 756 us, k_bucket_fill 218 us) against 0.19 ms.
+double grid_cell(const pncg_ctx* c) {
+  return std::max(c->cell_user, std::max(1.5 * c->lmean, c->dhat + c->skin));
+}
+
 int grid_for(const pncg_ctx* c) {
   long long work = std::max<long long>({(long long)c->nWaves * kWave, (long long)c->nT, (long long)c->nV, 1LL});
   long long g = (work + kSBlock - 1) / kSBlock;
@@ -1480,9 +1491,6 @@ int pncg_set_contact(pncg_ctx* c, double dhat, double kappa, double cell, int32_
   c->cell_user = cell;
   c->planes = P;
   c->cflags = flags;
-  // grid cell: the caller's, or 1.5 x the mean rest length of the surface
-  // edges (at least the candidate inflation), so each primitive touches a
-  // few cells and a cell holds a few primitives
   double lsum = 0.0;
   for (int e = 0; e < c->nE; ++e) {
     const int a = c->edges[2 * e], b = c->edges[2 * e + 1];
@@ -1493,7 +1501,7 @@ int pncg_set_contact(pncg_ctx* c, double dhat, double kappa, double cell, int32_
   const double lmean = c->nE > 0 ? lsum / c->nE : 0.0;
   c->lmean = lmean;
   c->skin = c->skin_user > 0.0 ? c->skin_user : default_skin(dhat, lmean);
-  c->cell = cell > 0.0 ? cell : std::max(1.5 * lmean, dhat + c->skin);
+  c->cell = grid_cell(c);
   c->n_excl_pt = c->n_excl_ee = 0;
   HIPCHK(c, hipSetDevice(c->device));
   if ((flags & PNCG_CONTACT_SELF) && (flags & PNCG_CONTACT_REST_EXCLUDE) && c->nF + c->nE > 0) {
@@ -1588,8 +1596,7 @@ int pncg_set_tuning(pncg_ctx* c, double skin, int32_t chunk) {
   c->skin_user = skin;
   c->list_valid = false;
   c->skin = skin > 0.0 ? skin : default_skin(c->dhat, c->lmean);
-  if (c->cell_user <= 0.0 && c->lmean > 0.0) c->cell = std::max(1.5 * c->lmean, c->dhat + c->skin);
-  else if (c->cell_user <= 0.0) c->cell = c->dhat + c->skin;
+  c->cell = grid_cell(c);
   if (chunk > 0) c->chunk = chunk;
   return PNCG_OK;
 }
