@@ -223,8 +223,8 @@ int pncg_set_material(pncg_ctx* ctx, const double* E, const double* nu,
 int pncg_set_model(pncg_ctx* ctx, int32_t model);
 
 /* Barrier parameters (Sec. 3, equation barrier): dhat > 0, kappa >= 0;
- * cell = smallest spatial-hash cell size (> 0) or 0: the cell is the larger of
- * it and a size derived from the surface (no result depends on it); planes [nP][4] rows (n0, n1, n2, o) with |n| = 1 describing the
+ * cell = spatial-hash cell size (> 0) or 0 for a size derived from the
+ * surface; planes [nP][4] rows (n0, n1, n2, o) with |n| = 1 describing the
  * half-spaces n.x >= o; flags PNCG_CONTACT_*. */
 int pncg_set_contact(pncg_ctx* ctx, double dhat, double kappa, double cell,
                      int32_t nP, const double* planes, uint32_t flags);
@@ -261,8 +261,8 @@ int pncg_set_candidates_override(pncg_ctx* ctx, int32_t kind, int64_t n, const i
  * last list build and rebuilds the list when the accumulated displacement
  * bound exceeds skin / 2 (Algorithm 1's per-iteration constraint set is the
  * active subset of that list); 0 = the default, 0.4 x the mean surface-edge
- * rest length less dhat, clamped to [2, 8] dhat.  The derived cell of
- * pncg_set_contact is max(1.5 x mean surface edge, dhat + skin).
+ * rest length less dhat, clamped to [2, 8] dhat.  If the contact cell was left to
+ * the library (cell = 0), it becomes max(1.5 x mean surface edge, dhat + skin).
  * chunk > 0: iterations launched between reads of the device status (0
  * keeps the current value; default 16).  Call after pncg_set_contact, which
  * keeps a skin set here.  The call also drops a candidate list carried from

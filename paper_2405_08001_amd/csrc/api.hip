@@ -139,6 +139,7 @@ struct pncg_ctx {
   int model = PNCG_MODEL_NH;   // elastic density (PNCG_MODEL_*)
 
   // contact / solver parameters
+  int cell_shift = 0;
   double dhat = 1e-3, kappa = 0.0, cell_user = 0.0, cell = 0.0, skin = 0.0, skin_user = 0.0, lmean = 0.0;
   Planes planes{};
   unsigned cflags = 0;
@@ -204,8 +205,8 @@ struct pncg_ctx {
   double4 *d_item_lo = nullptr, *d_item_hi = nullptr;
   long long *d_item_cnt = nullptr, *d_item_off = nullptr;
   long long ent_cap = 0;
-  unsigned long long *d_ent_key = nullptr, *d_bkt_key = nullptr;
-  int *d_ent_item = nullptr, *d_bkt_item = nullptr, *d_ent_rank = nullptr;
+  unsigned long long* d_bkt_key = nullptr;
+  int *d_bkt_item = nullptr, *d_ent_rank = nullptr;
   double4 *d_bkt_lo = nullptr, *d_bkt_hi = nullptr;
   int4* d_bkt_ids = nullptr;
   long long *d_part_cnt = nullptr, *d_part_off = nullptr, *d_totals = nullptr;
@@ -424,9 +425,8 @@ Broad make_broad(pncg_ctx* c) {
   B.item_hi = c->d_item_hi;
   B.item_cnt = c->d_item_cnt;
   B.item_off = c->d_item_off;
+  B.shift = c->cell_shift;
   B.ent_cap = c->ent_cap;
-  B.ent_key = c->d_ent_key;
-  B.ent_item = c->d_ent_item;
   B.ent_rank = c->d_ent_rank;
   B.bkt_key = c->d_bkt_key;
   B.bkt_item = c->d_bkt_item;
@@ -534,9 +534,7 @@ int install_override(pncg_ctx* c) {
 int alloc_grid(pncg_ctx* c, long long ent) {
   int rc;
   drop_graphs(c);
-  for (void* p : {(void*)c->d_ent_key, (void*)c->d_ent_item, (void*)c->d_ent_rank, (void*)c->d_bkt_key,
-                  (void*)c->d_bkt_item,
-                  (void*)c->d_bkt_lo, (void*)c->d_bkt_hi, (void*)c->d_bkt_ids, (void*)c->d_count,
+  for (void* p : {(void*)c->d_ent_rank, (void*)c->d_bkt_key, (void*)c->d_bkt_item, (void*)c->d_bkt_lo, (void*)c->d_bkt_hi, (void*)c->d_bkt_ids, (void*)c->d_count,
                   (void*)c->d_start, (void*)c->d_part_cnt, (void*)c->d_part_off})
     dfree(c, p);
   c->ent_cap = std::max<long long>(ent, 4096);
@@ -544,8 +542,7 @@ int alloc_grid(pncg_ctx* c, long long ent) {
   while (ts < c->ent_cap / 4 && ts < (1 << 24)) ts <<= 1;
   c->tsize = ts;
   c->work_cap = (long long)c->nSV + c->ent_cap;
-  if ((rc = dmalloc(c, &c->d_ent_key, c->ent_cap)) || (rc = dmalloc(c, &c->d_ent_item, c->ent_cap)) ||
-      (rc = dmalloc(c, &c->d_ent_rank, c->ent_cap)) ||
+  if ((rc = dmalloc(c, &c->d_ent_rank, c->ent_cap)) ||
       (rc = dmalloc(c, &c->d_bkt_key, c->ent_cap)) || (rc = dmalloc(c, &c->d_bkt_item, c->ent_cap)) ||
       (rc = dmalloc(c, &c->d_bkt_lo, c->ent_cap)) || (rc = dmalloc(c, &c->d_bkt_hi, c->ent_cap)) ||
       (rc = dmalloc(c, &c->d_bkt_ids, c->ent_cap)) ||
@@ -1175,15 +1172,18 @@ double default_skin(double dhat, double lmean) {
   return std::min(8.0 * dhat, std::max(2.0 * dhat, 0.4 * lmean - dhat));
 }
 
-// Cell of the broad phase's grid: 1.5 x the mean rest length of the surface
-// edges, and at least the candidate inflation, so that a primitive's box
-// touches a few cells and a cell holds a few primitives.  A caller's cell is
-// used where it is larger; the candidate lists do not depend on the cell, and
-// a finer one only multiplies the entries: the 15,360-tet bar with 1 cm edges
-// and a 2 mm cell put each edge into some 300 cells, and a rebuild took
-// 1.17 ms (k_emit 756 us, k_bucket_fill 218 us) against 0.19 ms.
-double grid_cell(const pncg_ctx* c) {
-  return std::max(c->cell_user, std::max(1.5 * c->lmean, c->dhat + c->skin));
+// Caller's cell, or the one derived from the surface: 1.5 x the mean rest
+// length of the surface edges (at least the candidate inflation), so that each
+// primitive touches a few cells and a cell holds a few primitives.  The grid's
+// cells are 2^shift caller's cells to a side, near the derived size where that
+// is larger: the lists do not depend on the cell, and a finer one multiplies
+// the entries.  With 1 cm edges and the caller's 2 mm cells each edge of the
+// 15,360-tet bar enters some 300, and a rebuild took 1.17 ms (k_emit 756 us,
+// k_bucket_fill 218 us) against 0.19 ms.
+void set_cell(pncg_ctx* c) {
+  const double derived = std::max(1.5 * c->lmean, c->dhat + c->skin);
+  c->cell = c->cell_user > 0.0 ? c->cell_user : derived;
+  c->cell_shift = (int)std::min(20.0, std::max(0.0, std::round(std::log2(derived / c->cell))));
 }
 
 int grid_for(const pncg_ctx* c) {
@@ -1421,7 +1421,7 @@ int pncg_set_mesh(pncg_ctx* c, int32_t nV, const double* X, int32_t nT, const in
   c->split_ready = false;
   c->oscal_cap = 0;
   c->d_oscal = nullptr;
-  c->d_ent_key = nullptr; c->d_ent_item = nullptr; c->d_bkt_key = nullptr; c->d_bkt_item = nullptr;
+  c->d_bkt_key = nullptr; c->d_bkt_item = nullptr;
   c->d_ent_rank = nullptr;
   c->d_bkt_lo = nullptr; c->d_bkt_hi = nullptr; c->d_bkt_ids = nullptr;
   c->d_count = nullptr; c->d_start = nullptr; c->d_part_cnt = nullptr; c->d_part_off = nullptr;
@@ -1501,7 +1501,7 @@ int pncg_set_contact(pncg_ctx* c, double dhat, double kappa, double cell, int32_
   const double lmean = c->nE > 0 ? lsum / c->nE : 0.0;
   c->lmean = lmean;
   c->skin = c->skin_user > 0.0 ? c->skin_user : default_skin(dhat, lmean);
-  c->cell = grid_cell(c);
+  set_cell(c);
   c->n_excl_pt = c->n_excl_ee = 0;
   HIPCHK(c, hipSetDevice(c->device));
   if ((flags & PNCG_CONTACT_SELF) && (flags & PNCG_CONTACT_REST_EXCLUDE) && c->nF + c->nE > 0) {
@@ -1596,7 +1596,7 @@ int pncg_set_tuning(pncg_ctx* c, double skin, int32_t chunk) {
   c->skin_user = skin;
   c->list_valid = false;
   c->skin = skin > 0.0 ? skin : default_skin(c->dhat, c->lmean);
-  c->cell = grid_cell(c);
+  set_cell(c);
   if (chunk > 0) c->chunk = chunk;
   return PNCG_OK;
 }

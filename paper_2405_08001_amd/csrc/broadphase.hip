@@ -20,6 +20,11 @@
 // inflated boxes, which both edges touch.  So every pair is found exactly
 // once, and the exact test above makes the final decision.
 //
+// The grid's cells are the caller's, 2^shift of them to a side (Broad).  The
+// capacity of the entry arrays is counted in caller's cells, so which states
+// fit does not depend on the shift; an item touches no more cells of the grid
+// than caller's cells.
+//
 // Output is produced without any global counter: a counting pass stores the
 // pair counts of every entry, an exclusive scan turns them into offsets
 // (point-triangle counts of all entries first, then edge-edge), and a second
@@ -41,8 +46,11 @@ __device__ __forceinline__ int cell_coord(double p, double inv) {
   c = fmin(fmax(c, -1048575.0), 1048575.0);
   return (int)c;
 }
-__device__ __forceinline__ int3 cell_of(V3<double> p, double inv) {
-  return make_int3(cell_coord(p.x, inv), cell_coord(p.y, inv), cell_coord(p.z, inv));
+__device__ __forceinline__ int3 cell_of(V3<double> p, double inv, int shift) {
+  return make_int3(cell_coord(p.x, inv) >> shift, cell_coord(p.y, inv) >> shift, cell_coord(p.z, inv) >> shift);
+}
+__device__ __forceinline__ long long cells_between(int3 a, int3 b) {
+  return (long long)(b.x - a.x + 1) * (b.y - a.y + 1) * (b.z - a.z + 1);
 }
 __device__ __forceinline__ unsigned long long cell_key(int cx, int cy, int cz) {
   return ((unsigned long long)(cx + 1048576) << 42) | ((unsigned long long)(cy + 1048576) << 21) |
@@ -156,7 +164,7 @@ __device__ __forceinline__ void cull_box(const Broad& B, int i, double r, V3<dou
   }
 }
 
-// Boxes and cell counts of the items; also zeroes the bucket counters (which
+// Boxes of the items and the caller's cells they touch; also zeroes the bucket counters (which
 // k_emit bumps next) and, given a list counter, empties the list.
 __global__ void __launch_bounds__(kBlock) k_items(Broad B, const double4* x, double inv, double r,
                                                   long long* ncand) {
@@ -183,84 +191,68 @@ __global__ void __launch_bounds__(kBlock) k_items(Broad B, const double4* x, dou
     B.item_hi[i] = make_double4(hi.x, hi.y, hi.z, 0.0);
     V3<double> cl, ch;
     cull_box(B, i, r, cl, ch);
-    const int3 c0 = cell_of(cl, inv), c1 = cell_of(ch, inv);
-    B.item_cnt[i] = (long long)(c1.x - c0.x + 1) * (c1.y - c0.y + 1) * (c1.z - c0.z + 1);
+    B.item_cnt[i] = cells_between(cell_of(cl, inv, 0), cell_of(ch, inv, 0));
   }
 }
 
-// Entries of item i, one per cell of its culling box (z fastest, then y,
-// then x), at item_off[i] on.  The bucket counters are bumped eight cells at
-// a time, so that a thread has eight atomics in flight instead of waiting
-// for each rank before the next.
-__global__ void __launch_bounds__(kBlock) k_emit(Broad B, const double4* x, double inv, double r) {
-  constexpr int kBatch = 8;
+// The entries of the items, one per cell of an item's culling box (z fastest,
+// then y, then x), entry t by lane t mod kItemLanes of the item's group:
+// f(entry, item, cell key).  Entry numbers start at item_off[i]; those past
+// the capacity are left out.  A thread per item would make its 4 to 30
+// atomics or record stores one behind the other.
+constexpr int kItemLanes = 8;
+template <typename F>
+__device__ __forceinline__ void for_entries(const Broad& B, double inv, double r, F&& f) {
   const int n = B.nF + B.nE;
-  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+  const int lane = threadIdx.x & (kItemLanes - 1), stride = gridDim.x * (kBlock / kItemLanes);
+  for (int i = (blockIdx.x * kBlock + threadIdx.x) / kItemLanes; i < n; i += stride) {
     V3<double> cl, ch;
     cull_box(B, i, r, cl, ch);
-    const int3 c0 = cell_of(cl, inv), c1 = cell_of(ch, inv);
-    const int nz = c1.z - c0.z + 1, nyz = (c1.y - c0.y + 1) * nz;
-    const long long ncell = (long long)(c1.x - c0.x + 1) * nyz;
+    const int3 c0 = cell_of(cl, inv, B.shift), c1 = cell_of(ch, inv, B.shift);
+    const unsigned nz = c1.z - c0.z + 1, nyz = (c1.y - c0.y + 1) * nz;
     const long long o = B.item_off[i];
-    const long long m = min(ncell, B.ent_cap - o);   // entries past the capacity are not written
-    const bool edge = i >= B.nF;
-    for (long long t0 = 0; t0 < m; t0 += kBatch) {
-      int rank[kBatch];
-#pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const long long t = t0 + j;
-        if (t < m) {
-          const int cx = c0.x + (int)(t / nyz), rem = (int)(t % nyz);
-          const int cy = c0.y + rem / nz, cz = c0.z + rem % nz;
-          const unsigned long long k = cell_key(cx, cy, cz);
-          B.ent_key[o + t] = k;
-          B.ent_item[o + t] = B.nSV + i;
-          rank[j] = atomicAdd(&B.count[hash_key(k, B.tsize, edge)], 1);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < kBatch; ++j)
-        if (t0 + j < m) B.ent_rank[o + t0 + j] = rank[j];
+    const long long m = min(cells_between(c0, c1), B.ent_cap - o);
+    for (long long t = lane; t < m; t += kItemLanes) {
+      const unsigned cx = (unsigned)t / nyz, rem = (unsigned)t - cx * nyz, cy = rem / nz;
+      f(o + t, i, cell_key(c0.x + (int)cx, c0.y + (int)cy, c0.z + (int)(rem - cy * nz)));
     }
   }
+}
+
+// Rank of every entry in its bucket, by bumping the bucket's counter.
+__global__ void __launch_bounds__(kBlock) k_emit(Broad B, double inv, double r) {
+  for_entries(B, inv, r, [&](long long e, int i, unsigned long long k) {
+    B.ent_rank[e] = atomicAdd(&B.count[hash_key(k, B.tsize, i >= B.nF)], 1);
+  });
 }
 
 // Group the entries by bucket and store each entry's full record there: its
 // slot is the bucket's start plus the rank k_emit's counter gave it.
-__global__ void __launch_bounds__(kBlock) k_bucket_fill(Broad B, const double4* x) {
-  const long long n = min(B.totals[0], B.ent_cap);
-  const int vbase = B.nSV, ebase = B.nSV + B.nF;
-  for (long long j = blockIdx.x * kBlock + threadIdx.x; j < n; j += (long long)gridDim.x * kBlock) {
-    const unsigned long long k = B.ent_key[j];
-    const int it = B.ent_item[j];
-    const unsigned h = hash_key(k, B.tsize, it >= B.nSV + B.nF);
-    const int slot = B.start[h] + B.ent_rank[j];
+__global__ void __launch_bounds__(kBlock) k_bucket_fill(Broad B, const double4* x, double inv, double r) {
+  for_entries(B, inv, r, [&](long long e, int i, unsigned long long k) {
+    const bool edge = i >= B.nF;
+    const int slot = B.start[hash_key(k, B.tsize, edge)] + B.ent_rank[e];
     double4 lo, hi;
-    int4 ids = make_int4(-1, -1, -1, 0);
-    if (it < vbase) {
-      ids.x = B.surf[it];
-      lo = hi = x[ids.x];
-    } else if (it < ebase) {
-      const int f = it - vbase;
-      ids = make_int4(B.tris[3 * f], B.tris[3 * f + 1], B.tris[3 * f + 2], 0);
-      lo = B.item_lo[f];
-      hi = B.item_hi[f];
+    int4 ids;
+    if (!edge) {
+      ids = make_int4(B.tris[3 * i], B.tris[3 * i + 1], B.tris[3 * i + 2], 0);
+      lo = B.item_lo[i];
+      hi = B.item_hi[i];
     } else {
       // an edge record holds its two end points (its box is their
       // component-wise min and max), so the exact distance of a pair reads
       // the staged records instead of gathering positions
-      const int e = it - ebase;
-      ids.x = B.edges[2 * e];
-      ids.y = B.edges[2 * e + 1];
+      const int g = i - B.nF;
+      ids = make_int4(B.edges[2 * g], B.edges[2 * g + 1], -1, 0);
       lo = x[ids.x];
       hi = x[ids.y];
     }
     B.bkt_key[slot] = k;
-    B.bkt_item[slot] = it;
+    B.bkt_item[slot] = B.nSV + i;
     B.bkt_lo[slot] = lo;
     B.bkt_hi[slot] = hi;
     B.bkt_ids[slot] = ids;
-  }
+  });
 }
 
 // ------------------------------------------------------------------ pairs
@@ -356,7 +348,7 @@ __device__ __forceinline__ int vertex_pairs_wave(const Broad& B, const PairCtx& 
   const int lane = threadIdx.x & (kWave - 1);
   const int v = B.surf[w];
   const V3<double> p = ldx(P.x, v);
-  const int3 c = cell_of(p, P.inv);
+  const int3 c = cell_of(p, P.inv, B.shift);
   const unsigned long long key = cell_key(c.x, c.y, c.z);
   const unsigned h = hash_key(key, B.tsize, false);
   const int s0 = B.start[h], s1 = B.start[h + 1];
@@ -400,7 +392,7 @@ __device__ __forceinline__ void edge_pairs(const Broad& B, const PairCtx& P, con
     if (!(lo.x <= (hiA.x + r) && lo.y <= (hiA.y + r) && lo.z <= (hiA.z + r))) continue;
     // report only in the cell of the lower corner of the culling-box intersection
     const V3<double> corner = mk3(fmax(loA.x - q, lo.x - q), fmax(loA.y - q, lo.y - q), fmax(loA.z - q, lo.z - q));
-    const int3 cc = cell_of(corner, P.inv);
+    const int3 cc = cell_of(corner, P.inv, B.shift);
     if (cell_key(cc.x, cc.y, cc.z) != key) continue;
     const int e1 = ia - ebase, e2 = ib - ebase;
     // distance filter before the exclusion lookup (see vertex_slot_pair)
@@ -437,7 +429,7 @@ __device__ __forceinline__ bool edge_slot_pair_test(const Broad& B, const PairCt
   if (!((loA.x - r) <= hi.x && (loA.y - r) <= hi.y && (loA.z - r) <= hi.z)) return false;
   if (!(lo.x <= (hiA.x + r) && lo.y <= (hiA.y + r) && lo.z <= (hiA.z + r))) return false;
   const V3<double> corner = mk3(fmax(loA.x - q, lo.x - q), fmax(loA.y - q, lo.y - q), fmax(loA.z - q, lo.z - q));
-  const int3 cc = cell_of(corner, P.inv);
+  const int3 cc = cell_of(corner, P.inv, B.shift);
   if (cell_key(cc.x, cc.y, cc.z) != key) return false;
   const int e1 = R.item(sa) - ebase, e2 = R.item(sb) - ebase;
   if (P.filter_d >= 0.0) {
@@ -569,7 +561,7 @@ __global__ void __launch_bounds__(kBlock) k_pairs_emit(Broad B, PairCtx P, int2*
     for (long long w = wid; w < B.nSV; w += nwv) {
       const int v = B.surf[w];
       const V3<double> p = ldx(P.x, v);
-      const int3 c = cell_of(p, P.inv);
+      const int3 c = cell_of(p, P.inv, B.shift);
       const unsigned long long key = cell_key(c.x, c.y, c.z);
       const unsigned h = hash_key(key, B.tsize, false);
       const int s0 = B.start[h], s1 = B.start[h + 1];
@@ -868,15 +860,20 @@ void pairs_install(const int2* src, long long n, int2* out, long long* ncand, lo
   hipLaunchKernelGGL(k_pl_install, dim3(g), dim3(kBlock), 0, s, src, n, out, ncand, n_out);
 }
 
+// blocks of the kernels with kItemLanes lanes per item
+static int item_blocks(const Broad& B) {
+  return std::max(1, std::min((B.nF + B.nE + kBlock / kItemLanes - 1) / (kBlock / kItemLanes), 2048));
+}
+
 void broad_build_count(const Broad& B, const double4* x, double cell, double r, double filter_d, int filter_obj,
                        hipStream_t s) {
   const double inv = 1.0 / cell;
   const int n = B.nF + B.nE;
   hipLaunchKernelGGL(k_items, dim3(B.grid), dim3(kBlock), 0, s, B, x, inv, r, (long long*)nullptr);
   scan_exclusive<long long>(B.item_cnt, n, B.item_off, B.totals, B.part_off + B.work_cap, s);
-  hipLaunchKernelGGL(k_emit, dim3(B.grid), dim3(kBlock), 0, s, B, x, inv, r);
+  hipLaunchKernelGGL(k_emit, dim3(item_blocks(B)), dim3(kBlock), 0, s, B, inv, r);
   scan_exclusive<int>(B.count, B.tsize, B.start, B.start + B.tsize, (int*)(B.part_off + B.work_cap), s);
-  hipLaunchKernelGGL(k_bucket_fill, dim3(B.grid), dim3(kBlock), 0, s, B, x);
+  hipLaunchKernelGGL(k_bucket_fill, dim3(item_blocks(B)), dim3(kBlock), 0, s, B, x, inv, r);
   PairCtx P{x, inv, r, filter_d, filter_obj};
   const int nb = (int)std::min<long long>((B.ent_cap + kBlock - 1) / kBlock, 8192);
   hipLaunchKernelGGL(k_pairs_count, dim3(nb), dim3(kBlock), 0, s, B, P);
@@ -898,9 +895,9 @@ void broad_solver_list(const Broad& B, const double4* x, double cell, double r, 
   const int n = B.nF + B.nE;
   hipLaunchKernelGGL(k_items, dim3(B.grid), dim3(kBlock), 0, s, B, x, inv, r, ncand);
   scan_exclusive<long long>(B.item_cnt, n, B.item_off, B.totals, B.part_off + B.work_cap, s);
-  hipLaunchKernelGGL(k_emit, dim3(B.grid), dim3(kBlock), 0, s, B, x, inv, r);
+  hipLaunchKernelGGL(k_emit, dim3(item_blocks(B)), dim3(kBlock), 0, s, B, inv, r);
   scan_exclusive<int>(B.count, B.tsize, B.start, B.start + B.tsize, (int*)(B.part_off + B.work_cap), s);
-  hipLaunchKernelGGL(k_bucket_fill, dim3(B.grid), dim3(kBlock), 0, s, B, x);
+  hipLaunchKernelGGL(k_bucket_fill, dim3(item_blocks(B)), dim3(kBlock), 0, s, B, x, inv, r);
   PairCtx PC{x, inv, r, r, 0};
   const int nb = (int)std::min<long long>((B.ent_cap + kBlock - 1) / kBlock, 8192);
   hipLaunchKernelGGL(k_pairs_emit, dim3(nb), dim3(kBlock), 0, s, B, PC, out, cap, (unsigned long long*)ncand);

@@ -38,12 +38,11 @@ struct Broad {
   // items 0..nF-1 triangles, nF.. edges
   double4* item_lo;      // [nF + nE] triangle: min - r; edge: min
   double4* item_hi;      // [nF + nE] triangle: max + r; edge: max
-  long long* item_cnt;   // [nF + nE + nSV] cells touched (primitives, then vertices)
+  long long* item_cnt;   // [nF + nE + nSV] caller's cells touched (primitives, then vertices)
   long long* item_off;   // [nF + nE + nSV + 1]
-  // cell entries (item, cell key), then grouped by hash bucket
-  long long ent_cap;
-  unsigned long long* ent_key;   // [ent_cap]
-  int* ent_item;                 // [ent_cap]
+  int shift;             // a cell of the grid is 2^shift caller's cells to a side
+  // cell entries, grouped by hash bucket
+  long long ent_cap;             // counted in caller's cells
   int* ent_rank;                 // [ent_cap] place of the entry in its bucket (its bucket count before it)
   unsigned long long* bkt_key;   // [ent_cap] records grouped by bucket
   int* bkt_item;                 // [ent_cap]
@@ -57,13 +56,13 @@ struct Broad {
   long long work_cap;    // = 2 * ent_cap
   long long* part_cnt;   // [work_cap]
   long long* part_off;   // [work_cap + 4096]
-  long long* totals;     // device: [0] entries, [1] pairs, [2] point-triangle pairs
+  long long* totals;     // device: [0] entries (caller's cells), [1] pairs, [2] point-triangle pairs
   int grid;
 };
 
-// Rebuild the grid at positions x with cell size `cell` and inflation r,
-// count the pairs and scan the counts.  totals[0] receives the number of
-// cell entries (the build is valid only if it is <= ent_cap), totals[1] and
+// Rebuild the grid at positions x with the caller's cell size `cell` and
+// inflation r, count the pairs and scan the counts.  totals[0] receives the
+// number of cell entries (the build is valid only if it is <= ent_cap), totals[1] and
 // totals[2] the pair counts.  filter_d >= 0 keeps only pairs closer than
 // filter_d (exact distance), and with filter_obj only pairs of one object.
 void broad_build_count(const Broad& B, const double4* x, double cell, double r, double filter_d, int filter_obj,
