@@ -3,12 +3,14 @@
     python -m paper_2405_08001_amd.build
 
 Every source under csrc/ is compiled with hipcc for gfx950 (side by side,
-into a temporary folder) and linked into paper_2405_08001_amd/libpncg.so.  Packed-FP32 instruction selection is
-disabled (-packed-fp32-ops) and float64/float32 global atomics are emitted as
-hardware atomics (-munsafe-fp-atomics).  The persistent iteration kernel is compiled
-without machine-level loop-invariant code motion: its loop holds the whole
-iteration, and the constants and addresses hoisted out of it cost 30 to 70
-vector registers, which spill (no spill without: 76-90 float, 96-127 double).
+into a temporary folder) and linked into paper_2405_08001_amd/libpncg.so.
+Packed-FP32 instruction selection is disabled (-packed-fp32-ops) and
+float64/float32 global atomics are emitted as hardware atomics
+(-munsafe-fp-atomics).  The persistent iteration kernel is compiled without
+machine-level loop-invariant code motion: its loop holds the whole iteration,
+and the constants and addresses hoisted out of it cost 30 to 70 vector
+registers of the 128 (without: 62-127 and no spill but in the contact forms,
+which spill up to 4 in float and 26 in double).
 """
 from __future__ import annotations
 

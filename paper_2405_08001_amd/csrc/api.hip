@@ -213,11 +213,11 @@ struct pncg_ctx {
   long long work_cap = 0;
   int grid = 1;
   // persistent iteration kernel: tables and exchange buffers (set_mesh)
-  bool persist_ok = false;      // the mesh has tables
+  bool persist_ok[2] = {false, false};   // the mesh has tables (by element form, see PersistTables)
   int persist_off = 0;          // after a timed-out meeting: steps that still use the per-iteration launches
   signed char persist_fit[3][2] = {{-1, -1}, {-1, -1}, {-1, -1}};   // by [model][self]: kernel fits (-1 not asked yet)
   int units = 0;                // compute units of the device
-  PersistArgs persist{};
+  PersistArgs persist[2];
   // adjoint (allocated on first use)
   bool adj_ready = false;
   bool adj_warm = false;       // start each adjoint CG from the previous call's lambda
@@ -736,12 +736,12 @@ int read_status(pncg_ctx* c) {
 // Whether the step's iterations can run in the persistent kernel.
 template <typename R>
 bool persist_usable(pncg_ctx* c, const Args<R>& A) {
-  if (!c->persist_ok || c->profiling || A.split || (A.self && !A.seg)) return false;
+  if (!c->persist_ok[persist_form(A.model)] || c->profiling || A.split || (A.self && !A.seg)) return false;
   if (c->persist_off > 0) return false;
   signed char& fit = c->persist_fit[A.model][A.self];
   if (fit < 0) {
     bool ok = false;
-    fit = persist_fits<R>(c->persist, A.model, A.self != 0, c->units, &ok) == hipSuccess && ok ? 1 : 0;
+    fit = persist_fits<R>(c->persist[persist_form(A.model)], A.model, A.self != 0, c->units, &ok) == hipSuccess && ok ? 1 : 0;
   }
   return fit == 1;
 }
@@ -819,9 +819,9 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
     // (it starts from a complete x_k: at the step's beginning, after a pause
     // or where it left off, not behind a chunk of launches)
     persist_now = may_persist && (k0 == 0 || mode0 != kModeNormal) && (!A.self || fused) &&
-                  held.acquire(c->device, c->persist.blocks, c->units);
+                  held.acquire(c->device, c->persist[0].blocks, c->units);
     if (persist_now) {
-      launch_persist<R>(A, c->persist, k0, mode0, c->stream);
+      launch_persist<R>(A, c->persist[persist_form(A.model)], k0, mode0, c->stream);
       launch_finalize<R>(A, x_out, v_out, c->stream);   // writes only if the step has stopped
       last_is_final = true;
       return std::min(k0 + kPersistMaxIters, c->iter_max + 1);
@@ -1198,17 +1198,17 @@ int grid_for(const pncg_ctx* c) {
 // Tables and exchange buffers of the persistent iteration kernel for the mesh
 // just committed (none if a block's share does not fit in LDS).
 static int setup_persist(pncg_ctx* c) {
-  c->persist_ok = false;
+  c->persist_ok[0] = c->persist_ok[1] = false;
   c->persist_off = 0;
   for (auto& m : c->persist_fit) m[0] = m[1] = -1;
   PersistTables T;
-  PersistArgs& P = c->persist;
-  const bool fp64 = c->precision == PNCG_FP64;
-  if (!persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, fp64, c->nF + c->nE > 0, T, P))
-    return PNCG_OK;
+  persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, c->precision == PNCG_FP64,
+                c->nF + c->nE > 0, T);
+  if (!T.ok[0] && !T.ok[1]) return PNCG_OK;
   std::vector<uint8_t> fl(c->vflag);
   for (int i : c->tris) fl[i] |= kPairVertex;
   for (int i : c->edges) fl[i] |= kPairVertex;
+  PersistArgs& P = T.form[0];
   int rc;
   auto put = [&](auto& vec, auto*& dst) -> int {
     using T_ = typename std::remove_reference<decltype(vec)>::type::value_type;
@@ -1220,15 +1220,25 @@ static int setup_persist(pncg_ctx* c) {
     return PNCG_OK;
   };
   if ((rc = put(T.blk, P.blk)) || (rc = put(T.loc_v, P.loc_v)) || (rc = put(T.tet_e, P.tet_e)) ||
-      (rc = put(T.tet_l, P.tet_l)) || (rc = put(T.lane, P.lane)) || (rc = put(T.dtet, P.dtet)) ||
-      (rc = put(T.dvert, P.dvert)) || (rc = put(fl, P.lflag)))
+      (rc = put(T.tet_l, P.tet_l)) || (rc = put(T.lane, P.lane)) || (rc = put(T.wave_last, P.wave_last)) ||
+      (rc = put(T.run, P.run)) || (rc = put(T.seg, P.seg)) || (rc = put(T.chunk, P.chunk)) || (rc = put(T.entry, P.entry)) ||
+      (rc = put(T.dtet, P.dtet)) || (rc = put(T.dvert, P.dvert)) || (rc = put(fl, P.lflag)))
     return rc;
   if ((rc = dmalloc(c, &P.slot_grad, 24 * (size_t)P.grid)) || (rc = dmalloc(c, &P.slot_dir, 9 * (size_t)P.grid)) ||
       (rc = dmalloc(c, &P.pgx, 9 * (size_t)c->nV)) || (rc = dmalloc(c, &P.ring, 1)))
     return rc;
   P.limit = PNCG_PERSIST_WAIT;
   persist_clear(P, c->nV, c->stream);
-  c->persist_ok = true;
+  // both forms share the tables and the buffers
+  c->persist[0] = c->persist[1] = P;
+  c->persist[1].chunks = T.form[1].chunks;
+  c->persist[1].elem_lds = T.form[1].elem_lds;
+  c->persist[1].cap_rp = T.form[1].cap_rp;
+  c->persist[1].cap_dg = T.form[1].cap_dg;
+  c->persist[1].at = T.form[1].at;
+  c->persist[1].lds = T.form[1].lds;
+  c->persist_ok[0] = T.ok[0];
+  c->persist_ok[1] = T.ok[1];
   return sync(c);
 }
 
@@ -1722,7 +1732,7 @@ static int ensure_scal(pncg_ctx* c) {
 // resident: another process holds part of the device): empty the exchange
 // buffers and leave the kernel out for a while.
 static void restart_launches(pncg_ctx* c) {
-  persist_clear(c->persist, c->nV, c->stream);
+  persist_clear(c->persist[0], c->nV, c->stream);
   c->persist_off = kPersistBackoff;
 }
 

@@ -191,6 +191,14 @@ __device__ __forceinline__ V3<R> shape_vec(const R* B, int a) {
   return a < 2 ? lo : hi;
 }
 
+// sum_j b_j col_j
+template <typename R>
+__device__ __forceinline__ V3<R> lin3(V3<R> b, const V3<R> (&col)[3]) {
+  return mk3(std::fma(b.z, col[2].x, std::fma(b.x, col[0].x, b.y * col[1].x)),
+             std::fma(b.z, col[2].y, std::fma(b.x, col[0].y, b.y * col[1].y)),
+             std::fma(b.z, col[2].z, std::fma(b.x, col[0].z, b.y * col[1].z)));
+}
+
 // Psi_3 and Psi_33 of the Neo-Hookean density times V_e:
 //   V Psi_3  = (V lam log J - V mu) / J
 //   V Psi_33 = (V mu + V lam (1 - log J)) / J^2
@@ -210,12 +218,11 @@ __device__ __forceinline__ void nh_coeffs(const Kin<R>& k, R vmu, R vlam, R& vps
 template <typename R>
 __device__ __forceinline__ void i23_grad_diag(const Kin<R>& k, R a2, R vpsi3, R vpsi33, V3<R> ba, V3<R>& g,
                                               V3<R>& dg) {
-  V3<R> Fb = ba.x * k.f[0] + ba.y * k.f[1] + ba.z * k.f[2];
-  V3<R> Cb = ba.x * k.c[0] + ba.y * k.c[1] + ba.z * k.c[2];
-  g = a2 * Fb + vpsi3 * Cb;
-  // (the fused order spelled out, so that every kernel rounds it alike)
-  R bb = a2 * std::fma(ba.z, ba.z, std::fma(ba.x, ba.x, ba.y * ba.y));
-  dg = mk3(bb + vpsi33 * Cb.x * Cb.x, bb + vpsi33 * Cb.y * Cb.y, bb + vpsi33 * Cb.z * Cb.z);
+  // (the fused operations spelled out, so that every kernel rounds them alike)
+  const V3<R> Fb = lin3(ba, k.f), Cb = lin3(ba, k.c);
+  g = mk3(std::fma(a2, Fb.x, vpsi3 * Cb.x), std::fma(a2, Fb.y, vpsi3 * Cb.y), std::fma(a2, Fb.z, vpsi3 * Cb.z));
+  const R bb = a2 * std::fma(ba.z, ba.z, std::fma(ba.x, ba.x, ba.y * ba.y));
+  dg = mk3(std::fma(vpsi33 * Cb.x, Cb.x, bb), std::fma(vpsi33 * Cb.y, Cb.y, bb), std::fma(vpsi33 * Cb.z, Cb.z, bb));
 }
 
 // dF columns for per-vertex directions p_a: d_j = sum_{a=1..3} (p_a - p_0) B[a-1][j]

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <cstdint>
+#include <memory>
 #include <vector>
 
 #include "internal.h"
@@ -22,14 +23,25 @@ struct PersistBlock {
   int v0, nv;             // vertices of the curvature pass
 };
 
+// One tet of a chunk of incidence waves: the lanes, counted from the chunk's
+// first, that its four corners' terms go to (kNone: a vertex of another chunk
+// or block).
+struct alignas(4) PersistEntry {
+  unsigned short slot[4];
+  unsigned short tet, pad;     // local tet
+};
+
 // Byte offsets of the arrays of a block in its dynamic LDS.  Local vertices
 // [cap_loc]: x, m (mass), p, pg, fl (flags); own ones [cap_own]: xt, xb (list
-// build positions), P (1 / diag), tot (element sums), g (two copies, by
-// iteration parity), ce (corner-entry range); the others: hv (global vertex).
-// Tets [cap_tet]: rec (record, kRec reals), tl (corners), te (global tet, where
-// the records stay in memory).
+// build positions), P (1 / diag), g (two copies, by iteration parity), ce
+// (corner-entry range), run (row runs); the others: hv (global vertex).  Tets [cap_tet]: rec (record, kRec
+// reals), tl (corners), te (global tet, where the records stay in memory).
+// res: the corner terms of a chunk's lanes; seg: the row runs; tot: the sums of
+// the row runs (by tet) or own vertices (by lane); lane: the block's lanes; wm:
+// its waves (wave_last); rp: run partials of the pair entries [cap_rp][6]; dg:
+// pairs of the curvature pass.
 struct PersistLayout {
-  unsigned x, m, xt, xb, P, tot, p, pg, g, rec, tl, te, hv, ce, lane, dt, dv, fl;
+  unsigned x, m, xt, xb, P, tot, p, pg, g, rec, tl, te, hv, ce, lane, dt, dv, fl, res, seg, run, wm, rp, dg;
 };
 
 struct PersistArgs {
@@ -39,6 +51,13 @@ struct PersistArgs {
   const int* tet_e;              // global tet of each local one
   const ushort4* tet_l;          // its corners as local vertices
   const ushort2* lane;           // [64 nWaves] {local tet << 2 | corner or kNone, local vertex | kLaneLast}
+  const ulonglong2* wave_last;   // [nWaves] {mask of the vertices' last lanes, first of them as a local vertex}
+  // row runs: the lanes of one vertex within one row of 16 lanes of a wave
+  const ushort2* seg;            // {last lane within the chunk, lanes before it}
+  const ushort2* run;            // [nV] {first row run in the block, number}
+  const int4* chunk;             // [blocks][chunks + 1] {first entry; first own vertex and row run in the
+                                 // block; first row run of the block}
+  const PersistEntry* entry;
   const unsigned short* dtet;    // [nT] local tet of each tet, in the block whose curvature pass takes it
   const unsigned short* dvert;   // [nV] local vertex of each vertex, likewise
   const uint8_t* lflag;          // [nV] vertex flags | kPairVertex
@@ -48,7 +67,9 @@ struct PersistArgs {
   unsigned long long* pgx;       // [3][nV][3]
   int* ring;                     // set of the next launch's first iteration
   long long limit;               // longest wait, in ticks of the 100 MHz clock
-  int cap_loc, cap_own, cap_tet, cap_lane, cap_dt, cap_dv;   // largest of each over the blocks
+  int cap_own;                   // most own vertices of a block
+  int chunks;                    // chunks of a block's waves
+  int cap_rp, cap_dg;            // pair entries whose run partials, and pairs whose geometry, fit in LDS
   int elem_lds;                  // element records in LDS (else read from memory)
   PersistLayout at;
   size_t lds;                    // dynamic LDS of a block
@@ -56,22 +77,43 @@ struct PersistArgs {
 
 constexpr unsigned short kNone = 0xffff;
 constexpr unsigned short kLaneVert = 0x7fff, kLaneLast = 0x8000;   // vertex of a lane (kLaneVert: none); its last lane
+constexpr int kMaxChunks = 8;
 constexpr int kRec = 12;              // reals of an element record in LDS (11, padded to 16 bytes)
+constexpr int kRunPartials = 256;     // pair entries of a block with run partials in LDS
+constexpr size_t kPairGeom = 88;      // bytes of a PairGeom (persist.hip); one wave of them per logical block
 constexpr uint8_t kPairVertex = 4;    // corner of a surface triangle or edge (beside kFixed, kSurface)
 constexpr size_t kPersistLds = 158 * 1024;   // of the 160 KiB of a compute unit, less the static arrays
 constexpr int kPersistMaxIters = 512;  // iterations of one launch (the host looks at the error bits between launches)
 
-// Host-built tables of PersistArgs; false where a block's share does not fit
-// (then the step uses the per-iteration launches).
+// Host-built tables of PersistArgs, and the layouts of the two element forms:
+// [0] by tet, [1] by (tet, corner) lane for the corotated models.
+// A table that is filled after it is sized (a vector would write it twice).
+template <typename T>
+struct PersistTable {
+  using value_type = T;
+  std::unique_ptr<T[]> d;
+  size_t n = 0;
+  void resize(size_t m) { d.reset(new T[m]); n = m; }
+  T* data() { return d.get(); }
+  size_t size() const { return n; }
+};
 struct PersistTables {
   std::vector<PersistBlock> blk;
-  std::vector<int> loc_v, tet_e;
-  std::vector<ushort4> tet_l;
-  std::vector<ushort2> lane;
-  std::vector<unsigned short> dtet, dvert;
+  PersistTable<int> loc_v, tet_e;
+  PersistTable<ushort4> tet_l;
+  PersistTable<ushort2> lane, seg;
+  std::vector<ushort2> run;
+  PersistTable<ulonglong2> wave_last;
+  std::vector<int4> chunk;
+  PersistTable<PersistEntry> entry;
+  PersistTable<unsigned short> dtet;
+  std::vector<unsigned short> dvert;
+  PersistArgs form[2];
+  bool ok[2];           // a block's share fits in LDS
 };
-bool persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc, const std::vector<int>& inc_vert,
-                   int grid, bool fp64, bool self, PersistTables& T, PersistArgs& P);
+inline int persist_form(int model) { return model == kModelCorot ? 1 : 0; }
+void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc, const std::vector<int>& inc_vert,
+                   int grid, bool fp64, bool self, PersistTables& T);
 // Fill the exchange buffers with the empty mark and reset the ring.
 void persist_clear(const PersistArgs& P, int nV, hipStream_t s);
 // Iterations [k0, k0 + kPersistMaxIters) of a step, or up to its stop, pause or

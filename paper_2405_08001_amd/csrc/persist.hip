@@ -13,6 +13,15 @@
 // block forms the direction p = -P g + beta p and the update x += alpha p of
 // all of them, so only P g crosses blocks, once per iteration.
 //
+// Element terms.  The launches evaluate a tet in each of its four corners'
+// lanes; here a block evaluates it once and leaves the corners' terms in LDS
+// slots, one per incidence lane, which are then added per vertex in the order
+// of the lanes' segmented sum (row_run_sum).  That takes 0.4 to 0.5 of the
+// element arithmetic for more LDS traffic; the slots hold a chunk of the
+// waves at a time where they do not all fit.  The corotated models keep the
+// lanes (see the element pass).  Waves that have pair terms of their own leave
+// the tets to the others.
+//
 // Meeting.  A block publishes its partial sums and P g with agent-scope
 // stores and polls the other blocks' by agent-scope loads, one round trip per
 // meeting.  Every 8-byte word is its own flag: a word that still holds the
@@ -31,6 +40,13 @@
 // the process hold.  A wait is bounded by the clock all the same; a launch
 // that runs out raises kErrSync, writes nothing, and the host runs the step
 // again with the per-iteration launches, which give the same bits.
+//
+// Measured, us per pass: by launches, here with element terms by lane, by tet:
+//   1,296 tets float64, 20 iterations           446   287   282
+//   13,182 tets corotated mixed, 25             546   486   455 (by lane)
+//   30,000 tets float64, 48                    1178   871   799
+//   110,000-tet pile mixed, 2 frames of 25     1534  1003   952
+//   21,000-tet pile float64, 2 frames of 25    1132   806   768
 #include <cfloat>
 #include <climits>
 
@@ -183,6 +199,63 @@ __device__ __forceinline__ Elem<R> element(KPtr<R> K, const unsigned char* lds, 
   return e;
 }
 
+// Closest points of a pair (point-triangle or edge-edge) at `pos`; false if it
+// is not active (pair_closest).
+template <typename R, typename Pos>
+__device__ __forceinline__ bool pair_at(const Args<R>& A, bool pt, const int (&iv)[4], const Pos& pos, Closest& c) {
+  V3<double> X[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) X[i] = pos(iv[i]);
+  c = pt ? closest_pt(X[0], X[1], X[2], X[3]) : closest_ee(X[0], X[1], X[2], X[3]);
+  if (!(c.d > 0.0)) {
+    raise_err(A.status, kErrPenetration);
+    return false;
+  }
+  return c.d < A.dhat;
+}
+
+// sum_i c_i p_{k+1}(iv_i) of a pair, its corners in any block: P g as sent
+// before the first meeting (it may still be on its way) and p_k as stored.
+// All words are asked for at once.  False if the wait runs out.
+template <typename R>
+__device__ __forceinline__ bool pair_dir(const int (&iv)[4], const double (&c)[4], const u64* pgx, const R4<R>* pk, R beta,
+                                         long long limit, V3<double>& sp) {
+  u64 w[12];
+  V3<R> p[4];
+#pragma unroll
+  for (int i = 0; i < 12; ++i) w[i] = ld_agent(pgx + 3 * (size_t)iv[i / 3] + i % 3);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) p[i] = ld3_agent(pk, iv[i]);
+  Wait t(limit);
+  for (;;) {
+    bool here = true;
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+      if (w[i] != kEmpty) continue;
+      w[i] = ld_agent(pgx + 3 * (size_t)iv[i / 3] + i % 3);
+      here = false;
+    }
+    if (here) break;
+    if (t.over()) return false;
+  }
+  sp = mk3(0.0, 0.0, 0.0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    V3<R> g;
+    from_word(w[3 * i], g.x); from_word(w[3 * i + 1], g.y); from_word(w[3 * i + 2], g.z);
+    sp = sp + c[i] * cast3<double>(direction(g, p[i], beta));
+  }
+  return true;
+}
+
+// A pair of the curvature pass, its closest points found before the first
+// meeting (v[0] < 0: not active).
+struct PairGeom {
+  double c[4], t[3], ca, cb;
+  int v[4];
+};
+static_assert(sizeof(PairGeom) == kPairGeom, "PairGeom size");
+
 // The arguments that the terms of a pair read.
 template <typename R>
 __device__ __forceinline__ Args<R> pair_args(KPtr<R> K) {
@@ -193,6 +266,63 @@ __device__ __forceinline__ Args<R> pair_args(KPtr<R> K) {
   a.kappa = K->A.kappa;
   a.flags = K->A.flags;
   return a;
+}
+
+// Sum of the values res[6 lane] over the lanes [hi - len, hi], all in one row
+// of 16, as seg_sum adds them: a balanced tree counted from the last lane.  16
+// lanes are read (the words before the first lane of the chunk are other
+// arrays of the block's LDS) and those before the run count as zero, so the
+// loads have constant offsets and none waits for another.
+template <typename R>
+__device__ __forceinline__ R row_run_sum(const R* res, int hi, int len) {
+  const R* p = res + 6 * hi;
+  R u[16];
+#pragma unroll
+  for (int t = 0; t < 16; ++t) u[t] = p[-6 * t];
+#pragma unroll
+  for (int t = 1; t < 16; ++t) u[t] = t <= len ? u[t] : R(0);
+#pragma unroll
+  for (int d = 1; d < 16; d *= 2) {
+#pragma unroll
+    for (int t = 0; t < 16; t += 2 * d) u[t] += u[t + d];
+  }
+  return u[0];
+}
+
+// The value of the lane whose number differs in bit 0, 1, 2 or 3.
+template <int BIT>
+__device__ __forceinline__ int lane_xor(int v) {
+  if constexpr (BIT == 0) return __builtin_amdgcn_update_dpp(0, v, 0xb1, 0xf, 0xf, false);   // quad_perm [1, 0, 3, 2]
+  if constexpr (BIT == 1) return __builtin_amdgcn_update_dpp(0, v, 0x4e, 0xf, 0xf, false);   // quad_perm [2, 3, 0, 1]
+  if constexpr (BIT == 2) {
+    // shifts by 4 within the row: left into the lower of each two quads, right into the upper
+    const int lo = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, false);
+    return __builtin_amdgcn_update_dpp(lo, v, 0x114, 0xf, 0xa, false);
+  }
+  return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false);                          // row rotated by 8
+}
+template <int BIT>
+__device__ __forceinline__ double lane_xor(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = lane_xor<BIT>((int)b), hi = lane_xor<BIT>((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// a summed over lane pairs (BIT) into the lanes with the bit clear, b into the others
+template <int BIT>
+__device__ __forceinline__ double pair_sums(double a, double b) {
+  const bool up = (threadIdx.x >> BIT) & 1;
+  return (up ? b : a) + lane_xor<BIT>(up ? a : b);
+}
+// Sums of six quantities over each row of 16 lanes, in the balanced order of
+// wave_sum (neighbouring lanes first).  Halving the number of quantities per
+// lane at each step instead of reducing each alone takes 43 instructions
+// against 72.  Lane l of a row's first eight (and of the second) receives
+// quantity l, for l < 6.
+__device__ __forceinline__ double row_sums6(const double (&q)[6]) {
+  const double ab = pair_sums<0>(q[0], q[1]), cd = pair_sums<0>(q[2], q[3]), ef = pair_sums<0>(q[4], q[5]);
+  const double abcd = pair_sums<1>(ab, cd), ef2 = ef + lane_xor<1>(ef);
+  const double all = pair_sums<2>(abcd, ef2);
+  return all + lane_xor<3>(all);
 }
 
 // Publish quantity q of a logical block: sh holds the wave results [wave][N]
@@ -216,18 +346,23 @@ __device__ __forceinline__ void gather(const u64* slot, int n, unsigned maxmask,
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
   const int nw = min(4, (n + kWave - 1) / kWave), tasks = N * nw;
   u64 a[T], b[T];
+#pragma unroll
+  for (int i = 0; i < T; ++i) {
+    const int t = wave + i * nwaves, j = (t % nw) * kWave + lane;
+    a[i] = t < tasks && j < n ? kEmpty : 0;
+    b[i] = t < tasks && j + kSBlock < n ? kEmpty : 0;
+  }
   Wait w(limit);
   bool odone = false;
   for (;;) {
+    // (only the words that have not arrived: polling all of them again would
+    // keep the memory busy with 10 MB per try)
     bool ok = true;
 #pragma unroll
     for (int i = 0; i < T; ++i) {
-      const int t = wave + i * nwaves;
-      a[i] = b[i] = 0;
-      if (t >= tasks) continue;
-      const int q = t / nw, j = (t - q * nw) * kWave + lane;
-      if (j < n) a[i] = ld_agent(slot + q * n + j);
-      if (j + kSBlock < n) b[i] = ld_agent(slot + q * n + j + kSBlock);
+      const int t = wave + i * nwaves, q = t / nw, j = (t - q * nw) * kWave + lane;
+      if (a[i] == kEmpty) a[i] = ld_agent(slot + q * n + j);
+      if (b[i] == kEmpty) b[i] = ld_agent(slot + q * n + j + kSBlock);
     }
     if (!odone) odone = other();
 #pragma unroll
@@ -279,11 +414,19 @@ template <typename R, int M, bool SELF, int MAXT = 2 * GradBlock<R, M>::value>
 __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
   constexpr int GB = GradBlock<R, M>::value, DB = DirBlock<R, M>::value;
   constexpr int GW = GB / kWave, DW = DB / kWave;
+  constexpr bool kTets = M != kModelCorot;   // element terms by tet, or by (tet, corner) lane
   extern __shared__ __align__(16) unsigned char lds[];
-  __shared__ double sh[2 * 8 * 8];
+  __shared__ double sh[2 * 8 * 24];
   __shared__ double shg[8 * 4];
+  __shared__ double planes[4 * kMaxPlanes];
+  __shared__ int count[2];       // active pairs and planes, by iteration parity
+  __shared__ u64 moved[2];       // largest squared displacement since the list build
   __shared__ Run run;
   __shared__ PersistBlock B;
+  __shared__ int4 chk[kMaxChunks + 1];   // of each chunk: first entry, own vertex, row run
+  __shared__ int ent[4];         // corner entries [b, e) of each logical block's vertices
+  __shared__ int slot_id[2];     // partial index of each logical block: the blockIdx of the launch that has it
+  __shared__ int busy[16];       // waves with pair work
   __shared__ int lblk[2][6];     // per logical block: incidence waves [b, e), tets [b, e), vertices [b, e)
   // thread, wave, and the wave's logical block within the block (vi) with the
   // thread's place in it (vt); taken anew by every phase
@@ -296,6 +439,14 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
 #define LDS_AT(T, field) reinterpret_cast<T*>(lds + K->P.at.field)
 
   int k0, lp, set0, own0;
+  PersistEntry entry0{};         // the thread's first entry of the first chunk
+  // Pair work of the thread, fixed for the launch: corner pci of the pair with
+  // corner vertices pw (the first corner entry that it evaluates), or, in the
+  // last wave of a logical block where that one has few entries (early, their
+  // number), the pair whose geometry it finds for the curvature pass.
+  int4 pw = make_int4(0, 0, 0, 0);
+  int pci = -1, early = 0;
+  int erank = 0, efree = 0;      // place of the wave among those that share the tets (-1: has pair work), their number
   bool pending = false;          // x_k already lacks nothing, but stems from alpha_{k-1} p_k of this launch
   {
     PHASE;
@@ -309,6 +460,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
     if (tid == 0) B = b;
     if (tid < 2) {
       const int L = lp * vb + min(tid, vb - 1);
+      slot_id[tid] = (L % (n / kXcds)) * kXcds + L / (n / kXcds);
       const long long q[3] = {K->A.nWaves, K->A.nT, K->A.nV};
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
@@ -320,6 +472,11 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
     // ---- where to begin
     StepStatus* st = K->A.status;
     IterScal* scal = K->A.scal;
+    if (tid < 4 * kMaxPlanes) planes[tid] = K->A.planes.p[tid >> 2][tid & 3];
+    if (tid < 2) {
+      count[tid] = 0;
+      moved[tid] = 0;
+    }
     if (tid == 0) {
       Run r{};
       if (k0 > 0) {
@@ -403,28 +560,94 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
         LDS_AT(int, te)[t] = e;
       }
     }
-    for (int i = tid; i < b.nw * kWave; i += BS) LDS_AT(ushort2, lane)[i] = K->P.lane[(size_t)b.w0 * kWave + i];
+    if constexpr (kTets) {
+      const int nc = K->P.chunks;
+      const int4* ck = K->P.chunk + lp * (nc + 1);
+      if (tid <= nc) chk[tid] = ck[tid];
+      for (int l = tid; l < b.nown; l += BS) LDS_AT(ushort2, run)[l] = K->P.run[own0 + l];
+      const int s0 = ck[nc].w;
+      for (int i = tid; i < ck[nc].z; i += BS) LDS_AT(ushort2, seg)[i] = K->P.seg[s0 + i];
+    } else {
+      for (int i = tid; i < b.nw * kWave; i += BS) LDS_AT(ushort2, lane)[i] = K->P.lane[(size_t)b.w0 * kWave + i];
+    }
+    for (int i = tid; i < b.nw; i += BS) LDS_AT(ulonglong2, wm)[i] = K->P.wave_last[b.w0 + i];
     for (int i = tid; i < b.nt; i += BS) LDS_AT(unsigned short, dt)[i] = K->P.dtet[b.t0 + i];
     for (int i = tid; i < b.nv; i += BS) LDS_AT(unsigned short, dv)[i] = K->P.dvert[b.v0 + i];
   }
-  // partial index of logical block i of this block: the blockIdx of the launch that has it
-  auto slot_of = [&](int n, int vb, int i) {
-    const int per = n / kXcds, L = fresh_s(lp) * vb + i;
-    return (L % per) * kXcds + L / per;
-  };
   auto set_of = [&](int it) { return fresh_s(set0 + it - k0) % 3; };
   // clear this block's words of iteration it's set
   auto clear = [&](int it) {
     PHASE;
     const int s = set_of(it);
-    if (tid < 8 * vb) st_agent(K->P.slot_grad + s * 8 * n + (tid & 7) * n + slot_of(n, vb, tid >> 3), kEmpty);
-    if (tid < 3 * vb) st_agent(K->P.slot_dir + s * 3 * n + (tid % 3) * n + slot_of(n, vb, tid / 3), kEmpty);
+    if (tid < 8 * vb) st_agent(K->P.slot_grad + s * 8 * n + (tid & 7) * n + slot_id[tid >> 3], kEmpty);
+    if (tid < 3 * vb) st_agent(K->P.slot_dir + s * 3 * n + (tid % 3) * n + slot_id[tid / 3], kEmpty);
     u64* w = K->P.pgx + 3 * ((size_t)s * K->A.nV + own0);
     for (int i = tid; i < 3 * B.nown; i += BS) st_agent(w + i, kEmpty);
   };
   __syncthreads();
   clear(k0 + 1);
   clear(k0 + 2);
+  if constexpr (SELF) {
+    PHASE;
+    if (tid < vb) {
+      const int wb = lblk[tid][0], we = lblk[tid][1];
+      ent[2 * tid] = wb < we ? K->A.wrange[wb].x : 0;
+      ent[2 * tid + 1] = wb < we ? K->A.wrange[we - 1].y : 0;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      // a logical block without vertices has no entries: an empty range beside the other's
+      if (vb == 2 && ent[2] >= ent[3]) ent[2] = ent[3] = ent[1];
+      if (vb == 2 && ent[0] >= ent[1]) ent[0] = ent[1] = ent[2];
+    }
+    __syncthreads();
+    const int e0 = ent[2 * vi], e1 = ent[2 * vi + 1];
+    int j = e0 < e1 ? ((e0 >> 6) + (vt >> 6)) * kWave + lane : e1;
+    if (j < e0 || j >= e1) j = -1;
+    const int chunks = e0 < e1 ? ((e1 - 1) >> 6) - (e0 >> 6) + 1 : 0;
+    const long long nq = min(K->A.ncand[0], K->A.cand_cap), pe = (4 * nq + n - 1) / n;
+    const bool geom = K->P.cap_dg > 0 && pe <= kWave;
+    // (one decision for the launch's blocks would not do: a block whose last
+    // waves have entries of their own finds the geometry in the curvature pass)
+    bool ge = geom && chunks < GW;
+    if (vb == 2) {
+      const int o0 = ent[2 - 2 * vi], o1 = ent[3 - 2 * vi];
+      ge = ge && (o0 < o1 ? ((o1 - 1) >> 6) - (o0 >> 6) + 1 : 0) < GW;
+    }
+    early = ge ? (int)pe : 0;
+    if (ge && vt >= GB - kWave) {
+      const long long eb = (long long)(lp * vb + vi) * pe, ee = min(eb + pe, 4 * nq);
+      j = eb + lane < ee ? (int)(eb + lane) : -1;
+      if (j >= 0 && (K->A.cent[j] & 3) != 0) j = -1;
+      // lanes without a pair
+      LDS_AT(PairGeom, dg)[vi * kWave + lane].v[0] = -1;
+    }
+    if (j >= 0) {
+      const int sl = K->A.cent[j];
+      pci = sl & 3;
+      pw = K->A.pv[sl >> 2];
+    }
+    const bool b = __any(pci >= 0);
+    if (lane == 0) busy[wave] = b ? 1 : 0;
+    __syncthreads();
+    int before = 0, total = 0;
+    for (int w = 0; w < nwaves; ++w) {
+      const int f = 1 - busy[w];
+      before += w < wave ? f : 0;
+      total += f;
+    }
+    efree = __builtin_amdgcn_readfirstlane(total > 0 ? total : nwaves);
+    erank = __builtin_amdgcn_readfirstlane(total == 0 ? wave : b ? -1 : before);
+  } else {
+    PHASE;
+    efree = nwaves;
+    erank = wave;
+  }
+  if constexpr (kTets) {
+    PHASE;
+    const int e = chk[0].x + erank * kWave + lane;
+    if (erank >= 0 && e < chk[1].x) entry0 = K->P.entry[e];
+  }
 
   int k = k0;
   int last_set = set0;      // set of the next launch
@@ -493,109 +716,185 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
       if (run.exit) break;
     }
 
-    // ---- pair terms of this block's vertices (block_pair_entries)
-    double npair = 0.0;
+    // ---- pair terms of this block's vertices (block_pair_entries), and the
+    // geometry of the curvature pass's pairs
     if constexpr (SELF) {
       PHASE;
       const PairPos<R> pos{((k & 1) != 0) != pending ? K->A.x1 : K->A.x0, (k & 1) ? K->A.p1 : K->A.p0, run.alpha,
                            pending ? 1 : 0};
-      const int wb = lblk[vi][0], we = lblk[vi][1];
-      if (wb < we) {
-        const int2* wrange = K->A.wrange;
-        const int e0 = wrange[wb].x, e1 = wrange[we - 1].y;
-        if (e0 < e1) {
-          const Args<R> pa = pair_args(K);
-          const int* cent = K->A.cent;
-          for (int m = (e0 >> 6) + (vt >> 6); m <= ((e1 - 1) >> 6); m += GW) {
-            const int j = m * kWave + lane;
-            const bool mine = j >= e0 && j < e1;
-            double val[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-            int key = -1 - lane;
-            if (mine) {
-              const int sl = cent[j];
-              const int q = sl >> 2, ci = sl & 3;
-              int iv[4];
-              Closest c;
-              const bool act = pair_closest(pa, q, pos, iv, c, -1);
-              key = pick4(iv, ci);
-              if (act) {
-                pair_grad_diag_corner(pa, c, ci, val);
-                if (ci == 0) npair += 1.0;
+      const Args<R> pa = pair_args(K);
+      const int e0 = ent[2 * vi], e1 = ent[2 * vi + 1];
+      if (e0 < e1) {
+        const int base = ent[0], in_lds = ent[2 * vb - 1] - base <= K->P.cap_rp;
+        const int m0 = (e0 >> 6) + (vt >> 6);
+        for (int m = m0; m <= ((e1 - 1) >> 6); m += GW) {
+          const int j = m * kWave + lane;
+          const bool mine = j >= e0 && j < e1;
+          double val[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+          int key = -1 - lane;
+          if (mine) {
+            int4 w = pw;
+            int ci = pci;
+            if (m != m0) {
+              const int sl = K->A.cent[j];
+              w = K->A.pv[sl >> 2];
+              ci = sl & 3;
+            }
+            const int iv[4] = {w.x, w.y, w.z, w.w >= 0 ? w.w : ~w.w};
+            Closest c;
+            key = pick4(iv, ci);
+            if (pair_at(pa, w.w >= 0, iv, pos, c)) {
+              pair_grad_diag_corner(pa, c, ci, val);
+              if (ci == 0) atomicAdd(&count[k & 1], 1);
+            }
+          }
+          const bool last = seg_sum(key, val);
+          if (mine && last) {
+            double* o = in_lds ? LDS_AT(double, rp) + 6 * (j - base) : K->A.rp + 6 * (size_t)j;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) o[i] = val[i];
+          }
+        }
+      }
+      if (early && vt >= GB - kWave && pci >= 0) {
+        const int iv[4] = {pw.x, pw.y, pw.z, pw.w >= 0 ? pw.w : ~pw.w};
+        Closest c;
+        PairGeom* g = LDS_AT(PairGeom, dg) + vi * kWave + lane;
+        const bool act = pair_at(pa, pw.w >= 0, iv, pos, c);
+        g->v[0] = act ? iv[0] : -1;
+        if (act) {
+          pair_hess_coefs(pa, c.d, g->ca, g->cb);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) { g->v[i] = iv[i]; g->c[i] = c.c[i]; }
+          g->t[0] = c.t.x; g->t[1] = c.t.y; g->t[2] = c.t.z;
+        }
+      }
+    }
+    // ---- element gradient and diagonal, summed per vertex; then the vertex
+    // terms (vertex_terms), one component to a thread: inertia, planes, pairs;
+    // g, P g = g / diag and 1 / diag.  The fused forms written out are those
+    // the compiler chooses in the per-iteration launches.
+    for (int c = 0;; ++c) {
+      {
+        PHASE;
+        const ushort4* tl = LDS_AT(ushort4, tl);
+        const double* X = LDS_AT(double, x);
+        if constexpr (kTets) {
+          // each tet of the chunk once, its corners' terms to the lanes of
+          // the chunk's vertices
+          R* res = LDS_AT(R, res);
+          const int e0 = chk[c].x + erank * kWave + lane, e1 = chk[c + 1].x;
+          for (int e = e0; erank >= 0 && e < e1; e += efree * kWave) {
+            const PersistEntry en = c == 0 && e == e0 ? entry0 : K->P.entry[e];
+            const ushort4 v = tl[en.tet];
+            const Elem<R> rec = element<R>(K, lds, en.tet);
+            const Kin<R> kin = kinematics<R>(rec.B, at3(X, v.x), at3(X, v.y), at3(X, v.z), at3(X, v.w));
+            bool ok = true;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+              const unsigned short to = en.slot[a];
+              if (to == kNone) continue;
+              V3<R> g, dg;
+              if (!el_grad_diag<R, M>(kin, rec.vmu, rec.vlam, shape_vec(rec.B, a), g, dg)) {
+                ok = false;
+                g = mk3(R(0), R(0), R(0));
+                dg = g;
+              }
+              R* o = res + 6 * to;
+              o[0] = g.x; o[1] = g.y; o[2] = g.z; o[3] = dg.x; o[4] = dg.y; o[5] = dg.z;
+            }
+            if (!ok) raise_err(K->A.status, kErrInverted);
+          }
+        } else {
+          // one (tet, corner) to a lane: the corotated terms' iteration count
+          // is voted by the wave, so the waves keep the incidence's lanes
+          const ushort2* lt = LDS_AT(ushort2, lane);
+          R* tot = LDS_AT(R, tot);
+          const int w0 = B.w0, we = lblk[vi][1];
+          for (int w = lblk[vi][0] + (vt >> 6); w < we; w += GW) {
+            const ushort2 ln = lt[(w - w0) * kWave + lane];
+            const int l = ln.y & kLaneVert;
+            R s[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
+            if (ln.x != kNone) {
+              const int t = ln.x >> 2;
+              const ushort4 v = tl[t];
+              const Elem<R> rec = element<R>(K, lds, t);
+              const Kin<R> kin = kinematics<R>(rec.B, at3(X, v.x), at3(X, v.y), at3(X, v.z), at3(X, v.w));
+              V3<R> g, dg;
+              if (el_grad_diag<R, M>(kin, rec.vmu, rec.vlam, shape_vec(rec.B, ln.x & 3), g, dg)) {
+                s[0] = g.x; s[1] = g.y; s[2] = g.z; s[3] = dg.x; s[4] = dg.y; s[5] = dg.z;
+              } else {
+                raise_err(K->A.status, kErrInverted);
               }
             }
-            const bool last = seg_sum(key, val);
-            if (mine && last) {
-              double* o = K->A.rp + 6 * (size_t)j;
+            seg_sum(l, s);
+            if (ln.y & kLaneLast) {
 #pragma unroll
-              for (int i = 0; i < 6; ++i) o[i] = val[i];
+              for (int i = 0; i < 6; ++i) tot[6 * l + i] = s[i];
             }
           }
         }
       }
-    }
-    // ---- element gradient and diagonal, summed per vertex
-    {
-      PHASE;
-      const ushort2* lt = LDS_AT(ushort2, lane);
-      const ushort4* tl = LDS_AT(ushort4, tl);
-      const double* X = LDS_AT(double, x);
-      R* tot = LDS_AT(R, tot);
-      const int w0 = B.w0, we = lblk[vi][1];
-      for (int w = lblk[vi][0] + (vt >> 6); w < we; w += GW) {
-        const ushort2 ln = lt[(w - w0) * kWave + lane];
-        const int l = ln.y & kLaneVert;
-        R s[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
-        if (ln.x != kNone) {
-          const int t = ln.x >> 2;
-          const ushort4 c = tl[t];
-          const Elem<R> rec = element<R>(K, lds, t);
-          const Kin<R> kin = kinematics<R>(rec.B, at3(X, c.x), at3(X, c.y), at3(X, c.z), at3(X, c.w));
-          V3<R> g, dg;
-          if (el_grad_diag<R, M>(kin, rec.vmu, rec.vlam, shape_vec(rec.B, ln.x & 3), g, dg)) {
-            s[0] = g.x; s[1] = g.y; s[2] = g.z; s[3] = dg.x; s[4] = dg.y; s[5] = dg.z;
-          } else {
-            raise_err(K->A.status, kErrInverted);
-          }
+      __syncthreads();
+      if constexpr (kTets) {
+        // a vertex's lanes row by row, one value of one row to a thread
+        PHASE;
+        const ushort2* seg = LDS_AT(ushort2, seg);
+        const R* res = LDS_AT(R, res);
+        R* tot = LDS_AT(R, tot);
+        const int t1 = 6 * chk[c + 1].z;
+        for (int t = 6 * chk[c].z + tid; t < t1; t += BS) {
+          const int q = t / 6;
+          const ushort2 r = seg[q];
+          tot[t] = row_run_sum(res + (t - 6 * q), r.x, r.y);
         }
-        seg_sum(l, s);
-        if (ln.y & kLaneLast) {
-#pragma unroll
-          for (int i = 0; i < 6; ++i) tot[6 * l + i] = s[i];
-        }
+        __syncthreads();
       }
-    }
-    __syncthreads();
-    // ---- vertex terms (vertex_terms), one component to a thread: inertia,
-    // planes, pairs; g, P g = g / diag and 1 / diag.  The fused forms written
-    // out are those the compiler chooses in the per-iteration launches.
-    double nplane = 0.0, dx = 0.0;
-    {
       PHASE;
+      int i0 = 0, i1 = 3 * B.nown;
+      if constexpr (kTets) {
+        i0 = 3 * chk[c].y;
+        i1 = 3 * chk[c + 1].y;
+      }
       const double *X = LDS_AT(double, x), *XT = LDS_AT(double, xt), *Ms = LDS_AT(double, m);
       double* Pd = LDS_AT(double, P);
-      const R* tot = LDS_AT(R, tot);
       R *pg = LDS_AT(R, pg), *G = LDS_AT(R, g) + ((k & 1) ? 3 * K->P.cap_own : 0);
       const uint8_t* fls = LDS_AT(uint8_t, fl);
       const double h2 = K->A.h2;
       u64* pgw = K->P.pgx + 3 * ((size_t)set_of(k) * K->A.nV + own0);
-      for (int i = tid; i < 3 * B.nown; i += BS) {
+      for (int i = i0 + tid; i < i1; i += BS) {
         const int l = i / 3, j = i - 3 * l;
         const uint8_t fl = fls[l];
         const double m = Ms[l];
-        double gd = fma(h2, double(tot[6 * l + j]), m * (X[i] - XT[i]));
-        double dd = fma(h2, double(tot[6 * l + 3 + j]), m);
+        R tg, td;
+        if constexpr (kTets) {
+          // the vertex's rows in turn
+          const ushort2 r = LDS_AT(ushort2, run)[l];
+          const R* tot = LDS_AT(R, tot) + 6 * r.x + j;
+          tg = td = R(0);
+          for (int q = 0; q < r.y; ++q) {
+            tg += tot[6 * q];
+            td += tot[6 * q + 3];
+          }
+        } else {
+          const R* tot = LDS_AT(R, tot) + 6 * l;
+          tg = tot[j];
+          td = tot[3 + j];
+        }
+        double gd = fma(h2, double(tg), m * (X[i] - XT[i]));
+        double dd = fma(h2, double(td), m);
         if (fl & kSurface) {
           const V3<double> x = at3(X, l);
           for (int a = 0; a < K->A.planes.n; ++a) {
-            const double pl[4] = {K->A.planes.p[a][0], K->A.planes.p[a][1], K->A.planes.p[a][2], K->A.planes.p[a][3]};
+            const double* pl = planes + 4 * a;
             const double d = plane_dist(pl, x), dhat = K->A.dhat;
             if (d < dhat) {
               if (!(d > 0.0)) { raise_err(K->A.status, kErrPenetration); continue; }
               const double b1 = K->A.kappa * barrier_db(d, dhat), b2 = K->A.kappa * barrier_d2b(d, dhat);
-              const double nj = j == 0 ? pl[0] : j == 1 ? pl[1] : pl[2];
+              const double nj = pl[j];
               gd = fma(b1, nj, gd);
               dd = fma(b2 * nj, nj, dd);
-              if (j == 0) nplane += 1.0;
+              if (j == 0) atomicAdd(&count[k & 1], 1);
             }
           }
         }
@@ -604,9 +903,11 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
           const int c0 = ce[0], c1 = ce[1];
           if (c0 < c1) {
             // the vertex's runs, one per 64-entry chunk (pair_partials_sum)
+            const int base = ent[0], in_lds = ent[2 * vb - 1] - base <= K->P.cap_rp;
             double ga = 0.0, da = 0.0;
             for (int q = c0 >> 6; q * kWave < c1; ++q) {
-              const double* rp = K->A.rp + 6 * (size_t)(min(c1, (q + 1) * kWave) - 1);
+              const int e = min(c1, (q + 1) * kWave) - 1;
+              const double* rp = in_lds ? LDS_AT(double, rp) + 6 * (e - base) : K->A.rp + 6 * (size_t)e;
               ga += rp[j];
               da += rp[3 + j];
             }
@@ -616,7 +917,9 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
           if ((fl & kSurface) && j == 0) {
             const double* XB = LDS_AT(double, xb);
             const double ex = X[i] - XB[i], ey = X[i + 1] - XB[i + 1], ez = X[i + 2] - XB[i + 2];
-            dx = fmax(dx, sqrt(fma(ez, ez, fma(ex, ex, ey * ey))));
+            // the square (positive doubles order as their bits; the root is monotonic)
+            const double e2 = fma(ez, ez, fma(ex, ex, ey * ey));
+            if (e2 > 0.0) atomicMax(&moved[k & 1], word(e2));
           }
           if (pending && (fl & kPairVertex)) st1_agent((k & 1) ? K->A.x1 : K->A.x0, own0 + l, j, X[i]);
         }
@@ -630,21 +933,22 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
         Pd[i] = 1.0 / dd;
         st_agent(pgw + i, pg_word(pgR));
       }
+      __syncthreads();
+      if (!kTets || c + 1 >= K->P.chunks) break;
     }
-    __syncthreads();
     // ---- dot products for beta, each vertex at the lane its sum ended on
     {
       PHASE;
-      const ushort2* lt = LDS_AT(ushort2, lane);
+      const ulonglong2* wm = LDS_AT(ulonglong2, wm);
       const double* Pd = LDS_AT(double, P);
       const R *pg = LDS_AT(R, pg), *p = LDS_AT(R, p), *G = LDS_AT(R, g);
       const R *gn = G + ((k & 1) ? 3 * K->P.cap_own : 0), *go = G + ((k & 1) ? 0 : 3 * K->P.cap_own);
-      double dots[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      double dots[6] = {0, 0, 0, 0, 0, 0};
       const int w0 = B.w0, we = lblk[vi][1];
       for (int w = lblk[vi][0] + (vt >> 6); w < we; w += GW) {
-        const unsigned short c = lt[(w - w0) * kWave + lane].y;
-        if (c & kLaneLast) {
-          const int i = 3 * (c & kLaneVert);
+        const ulonglong2 m = wm[w - w0];   // last lanes of the wave's vertices, and the first of them
+        if ((m.x >> lane) & 1) {
+          const int i = 3 * ((int)m.y + __popcll(m.x & ((1ull << lane) - 1)));
 #pragma unroll
           for (int j = 0; j < 3; ++j) {
             const double g = double(gn[i + j]), pgj = double(pg[i + j]), pp = double(p[i + j]), P = Pd[i + j];
@@ -658,13 +962,9 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
           }
         }
       }
-      dots[6] = nplane + npair;   // counts: exact in any order
-      dots[7] = dx;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const double r = i == 7 ? wave_max(dots[i]) : wave_sum(dots[i]);
-        if (lane == 0) sh[wave * 8 + i] = r;
-      }
+      // rows of 16 lanes: lane l of each row's first eight holds quantity l
+      const double r = row_sums6(dots);
+      if ((lane & 15) < 6) sh[wave * 24 + (lane >> 4) * 6 + (lane & 7)] = r;
     }
     __syncthreads();
     // ---- first meeting: the sums, and P g of the vertices shared with others
@@ -674,7 +974,18 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
       u64* slots = K->P.slot_grad + s * 8 * n;
       if (tid < 8 * vb) {
         const int i = tid >> 3, q = tid & 7;
-        publish<8>(sh + i * GW * 8, q, GW, q == 7, slots + q * n + slot_of(n, vb, i));
+        double r;
+        if (q < 6) {
+          // the rows of a wave as wave_sum adds them, then the waves
+          const double* h = sh + i * GW * 24 + q;
+          r = (h[18] + h[12]) + (h[6] + h[0]);
+          for (int w = 1; w < GW; ++w) r += (h[24 * w + 18] + h[24 * w + 12]) + (h[24 * w + 6] + h[24 * w]);
+        } else {
+          // counts and the maximum do not depend on the order: the block's go
+          // with its first logical block
+          r = i > 0 ? 0.0 : q == 6 ? double(count[k & 1]) : sqrt(as_double(moved[k & 1]));
+        }
+        st_agent(slots + q * n + slot_id[i], full(word(r)));
       }
       const u64* src = K->P.pgx + 3 * (size_t)s * K->A.nV;
       const int* hv = LDS_AT(int, hv);
@@ -759,6 +1070,11 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
     __syncthreads();
     last_set = set_of(k + 1);
     if (run.bad || run.exit) break;
+    if (threadIdx.x < 2) {
+      // (published; the next iteration counts in the other one)
+      if (threadIdx.x == 0) count[k & 1] = 0;
+      else moved[k & 1] = 0;
+    }
     // ---- p_{k+1} of every local vertex
     {
       PHASE;
@@ -817,7 +1133,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
           if (fls[l] & kSurface) {
             const V3<double> x = at3(X, l);
             for (int a = 0; a < K->A.planes.n; ++a) {
-              const double pl[4] = {K->A.planes.p[a][0], K->A.planes.p[a][1], K->A.planes.p[a][2], K->A.planes.p[a][3]};
+              const double* pl = planes + 4 * a;
               const double d = plane_dist(pl, x), dhat = K->A.dhat;
               if (d > 0.0 && d < dhat) {
                 const double np = fma(pl[2], pz, fma(pl[0], px, pl[1] * py));
@@ -833,44 +1149,43 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
       }
       if constexpr (SELF) {
         // the pairs of an even slice of the entry index (for_each_pair)
-        const Args<R> pa = pair_args(K);
-        const PairPos<R> pos{((k & 1) != 0) != pending ? K->A.x1 : K->A.x0, (k & 1) ? K->A.p1 : K->A.p0, run.alpha,
-                             pending ? 1 : 0};
         const u64* src = K->P.pgx + 3 * (size_t)set_of(k) * K->A.nV;
+        const R4<R>* pk = (k & 1) ? K->A.p1 : K->A.p0;
         const R rb = R(run.beta);
-        const long long nq = min(K->A.ncand[0], K->A.cand_cap);
-        const long long pe = (4 * nq + n - 1) / n;
-        const long long eb = (long long)(lp * vb + vi) * pe, ee = min(eb + pe, 4 * nq);
-        const int* cent = K->A.cent;
-        for (long long j = eb + vt; j < ee; j += DB) {
-          const int sl = cent[j];
-          if ((sl & 3) != 0) continue;
-          int iv[4];
-          Closest c;
-          if (!pair_closest(pa, sl >> 2, pos, iv, c, -1)) continue;
-          double ca, cb;
-          pair_hess_coefs(pa, c.d, ca, cb);
-          V3<double> sp = mk3(0.0, 0.0, 0.0);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            // every block has passed the first meeting, so P g of any vertex
-            // has been sent; it may still be on its way
-            u64 w[3];
-            Wait t(K->P.limit);
-            for (;;) {
-              bool here = true;
-#pragma unroll
-              for (int q = 0; q < 3; ++q) { w[q] = ld_agent(src + 3 * (size_t)iv[i] + q); here = here && w[q] != kEmpty; }
-              if (here) break;
-              if (t.over()) { run.bad = 1; break; }
+        const long long limit = K->P.limit;
+        if (early) {
+          if (vt < early) {
+            const PairGeom* g = LDS_AT(PairGeom, dg) + vi * kWave + vt;
+            const int iv[4] = {g->v[0], g->v[1], g->v[2], g->v[3]};
+            if (iv[0] >= 0) {
+              const double c[4] = {g->c[0], g->c[1], g->c[2], g->c[3]};
+              V3<double> sp;
+              if (!pair_dir<R>(iv, c, src, pk, rb, limit, sp)) run.bad = 1;
+              const double st = dot(sp, mk3(g->t[0], g->t[1], g->t[2]));
+              acc_pHp += g->ca * st * st + g->cb * dot(sp, sp);
             }
-            V3<R> pgv;
-            from_word(w[0], pgv.x); from_word(w[1], pgv.y); from_word(w[2], pgv.z);
-            const V3<R> q = direction(pgv, ld3_agent(pos.p, iv[i]), rb);
-            sp = sp + c.c[i] * cast3<double>(q);
           }
-          const double st = dot(sp, c.t);
-          acc_pHp += ca * st * st + cb * dot(sp, sp);
+        } else {
+          const Args<R> pa = pair_args(K);
+          const PairPos<R> pos{((k & 1) != 0) != pending ? K->A.x1 : K->A.x0, pk, run.alpha, pending ? 1 : 0};
+          const long long nq = min(K->A.ncand[0], K->A.cand_cap);
+          const long long pe = (4 * nq + n - 1) / n;
+          const long long eb = (long long)(lp * vb + vi) * pe, ee = min(eb + pe, 4 * nq);
+          const int* cent = K->A.cent;
+          for (long long j = eb + vt; j < ee; j += DB) {
+            const int sl = cent[j];
+            if ((sl & 3) != 0) continue;
+            const int4 w = K->A.pv[sl >> 2];
+            const int iv[4] = {w.x, w.y, w.z, w.w >= 0 ? w.w : ~w.w};
+            Closest c;
+            if (!pair_at(pa, w.w >= 0, iv, pos, c)) continue;
+            double ca, cb;
+            pair_hess_coefs(pa, c.d, ca, cb);
+            V3<double> sp;
+            if (!pair_dir<R>(iv, c.c, src, pk, rb, limit, sp)) run.bad = 1;
+            const double st = dot(sp, c.t);
+            acc_pHp += ca * st * st + cb * dot(sp, sp);
+          }
         }
       }
     }
@@ -892,7 +1207,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
       u64* slots = K->P.slot_dir + set_of(k) * 3 * n;
       if (tid < 3 * vb) {
         const int i = tid / 3, q = tid - 3 * i;
-        publish<3>(sh + i * GW * 3, q, DW, q > 0, slots + q * n + slot_of(n, vb, i));
+        publish<3>(sh + i * GW * 3, q, DW, q > 0, slots + q * n + slot_id[i]);
       }
       // ---- second meeting
       gather<3>(slots, n, 6u, shg, nwaves, K->P.limit, &run.bad, []() { return true; });
@@ -954,127 +1269,6 @@ hipError_t persist_fits(const PersistArgs& P, int model, bool self, int compute_
                                                   &per_cu, k_persist<R, M_, S_>, P.vb * GradBlock<R, M_>::value, P.lds))));
   *ok = e == hipSuccess && per_cu >= 1 && P.blocks <= compute_units;
   return e;
-}
-
-bool persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc, const std::vector<int>& inc_vert,
-                   int grid, bool fp64, bool self, PersistTables& T, PersistArgs& P) {
-  const int nWaves = (int)(inc.size() / kWave);
-  P = PersistArgs{};
-  P.grid = grid;
-  P.vb = grid > 256 ? 2 : 1;
-  P.blocks = grid / P.vb;
-  T = PersistTables{};
-  T.blk.resize(P.blocks);
-  T.lane.assign(inc.size(), make_ushort2(kNone, kLaneVert));
-  T.dtet.resize(nT);
-  T.dvert.resize(nV);
-  std::vector<int> vloc(nV, -1), vmark(nV, -1), tloc(nT, -1), tmark(nT, -1);
-  auto slice = [&](long long n, int L, int& b, int& e) {
-    const long long per = (n + grid - 1) / grid;
-    b = (int)std::min<long long>(L * per, n);
-    e = (int)std::min<long long>((L + 1) * per, n);
-  };
-  for (int p = 0; p < P.blocks; ++p) {
-    PersistBlock& B = T.blk[p];
-    int b0, e0, b1, e1;
-    slice(nWaves, p * P.vb, b0, e0);
-    slice(nWaves, p * P.vb + P.vb - 1, b1, e1);
-    B.w0 = b0; B.nw = e1 - b0;
-    slice(nT, p * P.vb, b0, e0);
-    slice(nT, p * P.vb + P.vb - 1, b1, e1);
-    B.t0 = b0; B.nt = e1 - b0;
-    slice(nV, p * P.vb, b0, e0);
-    slice(nV, p * P.vb + P.vb - 1, b1, e1);
-    B.v0 = b0; B.nv = e1 - b0;
-    B.loc_off = (int)T.loc_v.size();
-    B.tet_off = (int)T.tet_e.size();
-    int nl = 0, nt = 0;
-    auto vertex = [&](int v) {
-      if (vmark[v] != p) {
-        vmark[v] = p;
-        vloc[v] = nl++;
-        T.loc_v.push_back(v);
-      }
-      return vloc[v];
-    };
-    // own vertices: those of the block's incidence waves, consecutive
-    for (long long i = (long long)B.w0 * kWave; i < (long long)(B.w0 + B.nw) * kWave; ++i)
-      if (inc_vert[i] >= 0) vertex(inc_vert[i]);
-    B.nown = nl;
-    auto tet = [&](int e) {
-      if (tmark[e] != p) {
-        tmark[e] = p;
-        tloc[e] = nt++;
-        T.tet_e.push_back(e);
-        ushort4 c;
-        c.x = (unsigned short)vertex(tets[4 * e]);
-        c.y = (unsigned short)vertex(tets[4 * e + 1]);
-        c.z = (unsigned short)vertex(tets[4 * e + 2]);
-        c.w = (unsigned short)vertex(tets[4 * e + 3]);
-        T.tet_l.push_back(c);
-      }
-      return tloc[e];
-    };
-    for (long long i = (long long)B.w0 * kWave; i < (long long)(B.w0 + B.nw) * kWave; ++i) {
-      ushort2& l = T.lane[i];
-      if (inc_vert[i] >= 0) {
-        // a vertex's lanes are consecutive and within one wave
-        const bool last = (i + 1) % kWave == 0 || inc_vert[i + 1] != inc_vert[i];
-        l.y = (unsigned short)(vloc[inc_vert[i]] | (last ? kLaneLast : 0));
-      }
-      if (inc[i] >= 0) {
-        const int t = tet(inc[i] >> 2);
-        l.x = (unsigned short)(t << 2 | (inc[i] & 3));
-      }
-    }
-    for (int e = B.t0; e < B.t0 + B.nt; ++e) T.dtet[e] = (unsigned short)tet(e);
-    for (int v = B.v0; v < B.v0 + B.nv; ++v) T.dvert[v] = (unsigned short)vertex(v);
-    B.nloc = nl;
-    B.ntet = nt;
-    // 16-bit local ids; a lane's words also hold the corner (two bits) and the last-lane mark
-    if (nl >= kLaneVert || nt >= (kNone >> 2)) return false;
-    P.cap_loc = std::max(P.cap_loc, nl);
-    P.cap_own = std::max(P.cap_own, B.nown);
-    P.cap_tet = std::max(P.cap_tet, nt);
-    P.cap_lane = std::max(P.cap_lane, B.nw * kWave);
-    P.cap_dt = std::max(P.cap_dt, B.nt);
-    P.cap_dv = std::max(P.cap_dv, B.nv);
-    if (24 * (size_t)nl > kPersistLds) return false;
-  }
-  T.loc_v.push_back(0);   // a block without vertices reads its first one
-  // the layout of a block's LDS; element records in it if they fit
-  const unsigned real = fp64 ? 8 : 4;
-  for (int in_lds = 1; in_lds >= 0; --in_lds) {
-    size_t o = 0;
-    auto put = [&](unsigned& f, size_t bytes, size_t align) {
-      o = (o + align - 1) / align * align;
-      f = (unsigned)o;
-      o += bytes;
-    };
-    PersistLayout& L = P.at;
-    put(L.rec, in_lds ? kRec * real * (size_t)P.cap_tet : 0, 16);
-    put(L.x, 24 * (size_t)P.cap_loc, 8);
-    put(L.m, 8 * (size_t)P.cap_loc, 8);
-    put(L.xt, 24 * (size_t)P.cap_own, 8);
-    put(L.xb, self ? 24 * (size_t)P.cap_own : 0, 8);
-    put(L.P, 24 * (size_t)P.cap_own, 8);
-    put(L.tot, 6 * real * (size_t)P.cap_own, 8);
-    put(L.p, 3 * real * (size_t)P.cap_loc, 8);
-    put(L.pg, 3 * real * (size_t)P.cap_loc, 8);
-    put(L.g, 6 * real * (size_t)P.cap_own, 8);
-    put(L.tl, 8 * (size_t)P.cap_tet, 8);
-    put(L.te, in_lds ? 0 : 4 * (size_t)P.cap_tet, 4);
-    put(L.hv, 4 * (size_t)P.cap_loc, 4);
-    put(L.ce, self ? 8 * (size_t)P.cap_own : 0, 4);
-    put(L.lane, 4 * (size_t)P.cap_lane, 4);
-    put(L.dt, 2 * (size_t)P.cap_dt, 2);
-    put(L.dv, 2 * (size_t)P.cap_dv, 2);
-    put(L.fl, P.cap_loc, 1);
-    P.elem_lds = in_lds;
-    P.lds = o;
-    if (o <= kPersistLds) return true;
-  }
-  return false;
 }
 
 template void launch_persist<float>(const Args<float>&, const PersistArgs&, int, int, hipStream_t);

@@ -57,6 +57,17 @@ def test_bits_over_sizes(dims, precision):
     assert all(s["iters"] == 20 for s in st)
 
 
+# element terms in one to six chunks, with the records in LDS or in memory, and
+# a mesh whose share fits by lane only (mixed: 2 chunks in LDS, 1, 2, 2 and 3
+# in memory; float64: 2, 3, by lane or launches, 6, launches)
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("model", ["nh", "fcr"])
+@pytest.mark.parametrize("dims", [(50, 17, 17), (26, 26, 27), (28, 28, 28), (150, 13, 13), (200, 12, 12)])
+def test_bits_over_element_chunks(dims, model, precision):
+    sc, v0 = _block(*dims)
+    _same(sc, sc.X, v0, 1, precision, iter_max=6, eps=0.0, term="delta_e", model=model)
+
+
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("model", ["nh", "snh", "arap", "fcr"])
 def test_bits_over_materials(model, precision):
