@@ -387,9 +387,9 @@ int pncg_min_distance(pncg_ctx* ctx, const double* x, double* dmin,
 
 /* Per-kernel timing of steps (tracing aid).  With profiling on, every
  * launch a step makes is bracketed by HIP events recorded on the context's
- * stream, and the iterations are launched one by one (otherwise one launch
- * runs many of them where the mesh and the contact allow; the results are the
- * same bits); durations are summed per kind:
+ * stream, and the iterations, also the adjoint's, are launched one by one
+ * (otherwise one launch runs many of them where the mesh and the contact
+ * allow; the results are the same bits); durations are summed per kind:
  *   PNCG_PROF_NARROW  first launch of an iteration with self contact
  *                     under the atomic scatter or with
  *                     PNCG_SPLIT_OBJECTS (update + pair gradient/diagonal)

@@ -6,9 +6,9 @@ Every source under csrc/ is compiled with hipcc for gfx950 (side by side,
 into a temporary folder) and linked into paper_2405_08001_amd/libpncg.so.
 Packed-FP32 instruction selection is disabled (-packed-fp32-ops) and
 float64/float32 global atomics are emitted as hardware atomics
-(-munsafe-fp-atomics).  The persistent iteration kernel is compiled without
-machine-level loop-invariant code motion: its loop holds the whole iteration,
-and the constants and addresses hoisted out of it cost 30 to 70 vector
+(-munsafe-fp-atomics).  The persistent kernels are compiled without
+machine-level loop-invariant code motion: their loops hold a whole iteration,
+and the constants and addresses hoisted out cost the step kernel 30 to 70 vector
 registers of the 128 (without: 62-127 and no spill but in the contact forms,
 which spill up to 4 in float and 26 in double).
 """
@@ -41,7 +41,7 @@ def flags():
             "-Wno-unused-result", "-I" + os.path.join(HERE, "..", "include")]
 
 
-EXTRA_FLAGS = {"persist.hip": ["-mllvm", "-disable-machine-licm"]}
+EXTRA_FLAGS = {name: ["-mllvm", "-disable-machine-licm"] for name in ("persist.hip", "adjoint_persist.hip")}
 
 
 def _run(cmd, verbose):

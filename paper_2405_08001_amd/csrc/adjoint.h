@@ -5,6 +5,7 @@
 #pragma once
 
 #include "internal.h"
+#include "persist.h"
 
 namespace pncg {
 
@@ -21,7 +22,7 @@ struct CgStatus {
   int stopped;   // CG has ended
   int iters;     // CG iterations made (updates of lambda)
   int reason;    // 0 residual rule, 1 iteration cap, 2 p^T H p <= 0 or not finite
-  int pad;
+  int sync;      // a meeting of the persistent kernel timed out
   double bb;     // |b|^2 (= |r_0|^2)
   double rr;     // |r|^2 at the end
 };
@@ -55,6 +56,12 @@ void launch_adj_init(const Args<double>& A, const AdjArgs& C, const double* xbar
 // Otherwise a direction launch, the pair H p into acc, the Hv sweep and the
 // update launch; launches 0 .. max_iter.
 void launch_cg_iteration(const Args<double>& A, const AdjArgs& C, int k, bool fused, hipStream_t s);
+// Launches k0 .. k0 + kPersistMaxIters - 1 of the fused form, or up to the stop,
+// as one persistent launch; lambda goes to C.r (at k0 > 0 it also comes from
+// there).  Neo-Hookean and stable Neo-Hookean only: the corotated product's
+// bits depend on the lanes that share a wave.
+void launch_cg_persist(const Args<double>& A, const AdjArgs& C, const CgPersist& P, int k0, hipStream_t s);
+hipError_t cg_persist_fits(const CgPersist& P, int model, int compute_units, bool* ok);
 // xbar_t = M lambda - vbar / h, vbar_t = h M lambda; Ebar[e] -= lambda . dG/dE_e.
 void launch_adj_out(const Args<double>& A, const AdjArgs& C, const double* vbar, const double* E, double* xbar_t,
                     double* vbar_t, double* Ebar, hipStream_t s);

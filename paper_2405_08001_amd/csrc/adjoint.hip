@@ -12,9 +12,10 @@
 // Hessian-vector product h^2 V dP(dF) b_a (Sec. 3.1), inertia M, the plane
 // barrier kappa b''(d) n n^T (exact), and the pair terms as the solver's
 // pair Hessian model (Sec. 3.2, equations eq9/eq12).  The system is solved by
-// Jacobi-preconditioned linear CG.  Without pair terms an iteration is one
-// launch (k_cg_fused): it finishes the previous update lazily, forms the new
-// direction on the fly and applies H; with pair terms it is a direction
+// Jacobi-preconditioned linear CG.  Without pair terms the iterations run in
+// one persistent launch where the mesh fits (adjoint_persist.hip), else one
+// launch each (k_cg_fused): it finishes the previous update lazily, forms the
+// new direction on the fly and applies H; with pair terms it is a direction
 // launch, the pair H p, the Hv sweep and the update of lambda, r, z.  Global
 // scalars are per-block partials re-reduced by the next launch in a fixed
 // order, so every block takes the same decisions.
@@ -81,6 +82,7 @@ __global__ void __launch_bounds__(kSBlock) k_adj_init(Args<double> A, AdjArgs C,
   __shared__ double sh[kSWaves * 3];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     C.status->stopped = 0;
+    C.status->sync = 0;
     C.status->iters = 0;
     C.status->reason = 0;
     C.status->bb = 0.0;

@@ -218,6 +218,9 @@ struct pncg_ctx {
   signed char persist_fit[3][2] = {{-1, -1}, {-1, -1}, {-1, -1}};   // by [model][self]: kernel fits (-1 not asked yet)
   int units = 0;                // compute units of the device
   PersistArgs persist[2];
+  CgPersist cg_persist;         // the adjoint's, on the same tables
+  bool cg_persist_ok = false;
+  signed char cg_persist_fit[3] = {-1, -1, -1};   // by model
   // adjoint (allocated on first use)
   bool adj_ready = false;
   bool adj_warm = false;       // start each adjoint CG from the previous call's lambda
@@ -1088,6 +1091,25 @@ int ensure_adjoint(pncg_ctx* c, int cg_max) {
   return PNCG_OK;
 }
 
+// Whether the adjoint's CG iterations can run in their persistent kernel.
+bool cg_persist_usable(pncg_ctx* c, const Args<double>& A) {
+  if (!c->cg_persist_ok || A.model == kModelCorot || c->profiling || c->persist_off > 0) return false;
+  signed char& fit = c->cg_persist_fit[A.model];
+  if (fit < 0) {
+    bool ok = false;
+    fit = cg_persist_fits(c->cg_persist, A.model, c->units, &ok) == hipSuccess && ok ? 1 : 0;
+  }
+  return fit == 1;
+}
+
+// After a meeting of a persistent kernel timed out (its blocks were not all
+// resident: another process holds part of the device): empty the exchange
+// buffers and leave the kernels out for a while.
+void restart_launches(pncg_ctx* c) {
+  persist_clear(c->persist[0], c->nV, c->stream);
+  c->persist_off = kPersistBackoff;
+}
+
 // All pointers are device pointers.  Ebar is accumulated.
 int adjoint_impl(pncg_ctx* c, const double* x1, double h, const double* xbar, const double* vbar, double cg_tol,
                  int cg_max, double* xbar_t, double* vbar_t, double* Ebar, pncg_adjoint_stats* st) {
@@ -1121,20 +1143,40 @@ int adjoint_impl(pncg_ctx* c, const double* x1, double h, const double* xbar, co
   C.max_iter = cg_max;
   const bool fused = !A.self;
   const bool warm = fused && c->adj_warm && c->adj_lam_valid;
-  if (warm) HIPCHK(c, hipMemsetAsync(&c->d_cgst->stopped, 0, sizeof(int), c->stream));
-  launch_adj_init(A, C, xbar, vbar, warm, c->stream);
   const int last = fused ? cg_max + 1 : cg_max;   // the launch that reports the end at the latest
-  int k = 0, chunk = 16;
+  // the persistent kernel where it can take the iterations (as in the steps)
+  UnitsHeld held;
+  bool persist = fused && cg_persist_usable(c, A) && held.acquire(c->device, c->cg_persist.P.blocks, c->units);
   while (true) {
-    const int kend = std::min(k + chunk, last + 1);
-    for (int j = k; j < kend; ++j) launch_cg_iteration(A, C, j, fused, c->stream);
-    HIPCHK(c, hipMemcpyAsync(c->h_cgst, c->d_cgst, sizeof(CgStatus), hipMemcpyDeviceToHost, c->stream));
-    if ((rc = sync(c))) return rc;
-    if (c->h_cgst->stopped) break;
-    if (kend > last) return fail(c, PNCG_E_HIP, "adjoint CG did not report its end");
-    k = kend;
-    chunk = std::min(chunk * 2, 256);
+    if (warm) HIPCHK(c, hipMemsetAsync(&c->d_cgst->stopped, 0, sizeof(int), c->stream));
+    launch_adj_init(A, C, xbar, vbar, warm, c->stream);
+    int k = 0, chunk = 16;
+    while (true) {
+      const int kend = std::min(k + (persist ? kPersistMaxIters : chunk), last + 1);
+      if (persist) launch_cg_persist(A, C, c->cg_persist, k, c->stream);
+      else
+        for (int j = k; j < kend; ++j) launch_cg_iteration(A, C, j, fused, c->stream);
+      HIPCHK(c, hipMemcpyAsync(c->h_cgst, c->d_cgst, sizeof(CgStatus), hipMemcpyDeviceToHost, c->stream));
+      if ((rc = sync(c))) return rc;
+      if (c->h_cgst->stopped || c->h_cgst->sync) break;
+      if (kend > last) return fail(c, PNCG_E_HIP, "adjoint CG did not report its end");
+      k = kend;
+      chunk = std::min(chunk * 2, 256);
+    }
+    if (!persist) break;
+    held.release();
+    if (!c->h_cgst->sync) {
+      // lambda is in the other buffer
+      std::swap(c->d_lam, c->d_r);
+      C.lam = c->d_lam;
+      C.r = c->d_r;
+      break;
+    }
+    // a meeting timed out: once more with the per-iteration launches
+    restart_launches(c);
+    persist = false;
   }
+  if (c->persist_off > 0) --c->persist_off;
   const CgStatus cs = *c->h_cgst;
   if (st) {
     st->cg_iters = cs.iters;
@@ -1199,7 +1241,9 @@ int grid_for(const pncg_ctx* c) {
 // just committed (none if a block's share does not fit in LDS).
 static int setup_persist(pncg_ctx* c) {
   c->persist_ok[0] = c->persist_ok[1] = false;
+  c->cg_persist_ok = false;
   c->persist_off = 0;
+  for (auto& m : c->cg_persist_fit) m = -1;
   for (auto& m : c->persist_fit) m[0] = m[1] = -1;
   PersistTables T;
   persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, c->precision == PNCG_FP64,
@@ -1239,6 +1283,9 @@ static int setup_persist(pncg_ctx* c) {
   c->persist[1].lds = T.form[1].lds;
   c->persist_ok[0] = T.ok[0];
   c->persist_ok[1] = T.ok[1];
+  c->cg_persist = T.cg;
+  c->cg_persist.P = P;
+  c->cg_persist_ok = T.cg_ok;
   return sync(c);
 }
 
@@ -1726,14 +1773,6 @@ static int ensure_scal(pncg_ctx* c) {
   c->scal_cap = c->iter_max + 2;
   HIPCHK(c, hipMemsetAsync(c->d_scal, 0, sizeof(IterScal) * c->scal_cap, c->stream));
   return PNCG_OK;
-}
-
-// After a meeting of the persistent kernel timed out (its blocks were not all
-// resident: another process holds part of the device): empty the exchange
-// buffers and leave the kernel out for a while.
-static void restart_launches(pncg_ctx* c) {
-  persist_clear(c->persist[0], c->nV, c->stream);
-  c->persist_off = kPersistBackoff;
 }
 
 static int step_dev(pncg_ctx* c, const double* x, const double* v, double h, double* x_out, double* v_out,

@@ -191,6 +191,14 @@ __device__ __forceinline__ V3<R> shape_vec(const R* B, int a) {
   return a < 2 ? lo : hi;
 }
 
+// dot and cross with the fused operations spelled out
+template <typename R>
+__device__ __forceinline__ R fdot(V3<R> a, V3<R> b) { return std::fma(a.z, b.z, std::fma(a.x, b.x, a.y * b.y)); }
+template <typename R>
+__device__ __forceinline__ V3<R> fcross(V3<R> a, V3<R> b) {
+  return mk3(std::fma(a.y, b.z, -(a.z * b.y)), std::fma(a.z, b.x, -(a.x * b.z)), std::fma(a.x, b.y, -(a.y * b.x)));
+}
+
 // sum_j b_j col_j
 template <typename R>
 __device__ __forceinline__ V3<R> lin3(V3<R> b, const V3<R> (&col)[3]) {
@@ -257,6 +265,35 @@ __device__ __forceinline__ V3<R> i23_Hp(const Kin<R>& k, R a2, R vpsi3, R vpsi33
   V3<R> cb = ba.x * k.c[0] + ba.y * k.c[1] + ba.z * k.c[2];
   V3<R> dcb = ba.x * dc0 + ba.y * dc1 + ba.z * dc2;
   return a2 * db + (vpsi33 * cd) * cb + vpsi3 * dcb;
+}
+
+// The same in two parts, what the corners of a tet share and a corner's, with
+// the fused operations spelled out as the compiler chooses them for i23_Hp in
+// the adjoint's CG iteration.
+template <typename R>
+struct HpTet {
+  R s;          // Psi_33 (cof F : dF)
+  V3<R> d[3], dc[3];   // dF, dcof
+};
+template <typename R>
+__device__ __forceinline__ HpTet<R> i23_Hp_tet(const Kin<R>& k, const R* B, R vpsi33, V3<R> p0, V3<R> p1, V3<R> p2,
+                                               V3<R> p3) {
+  HpTet<R> h;
+  const V3<R> q[3] = {p1 - p0, p2 - p0, p3 - p0};
+#pragma unroll
+  for (int j = 0; j < 3; ++j) h.d[j] = lin3(mk3(B[j], B[3 + j], B[6 + j]), q);
+  const V3<R>(&d)[3] = h.d;
+  h.s = vpsi33 * (fdot(k.c[2], d[2]) + (fdot(k.c[0], d[0]) + fdot(k.c[1], d[1])));
+  h.dc[0] = fcross(d[1], k.f[2]) + fcross(k.f[1], d[2]);
+  h.dc[1] = fcross(d[2], k.f[0]) + fcross(k.f[2], d[0]);
+  h.dc[2] = fcross(d[0], k.f[1]) + fcross(k.f[0], d[1]);
+  return h;
+}
+template <typename R>
+__device__ __forceinline__ V3<R> i23_Hp_corner(const Kin<R>& k, const HpTet<R>& h, R a2, R vpsi3, V3<R> ba) {
+  const V3<R> db = lin3(ba, h.d), cb = lin3(ba, k.c), dcb = lin3(ba, h.dc);
+  return mk3(std::fma(vpsi3, dcb.x, std::fma(a2, db.x, h.s * cb.x)), std::fma(vpsi3, dcb.y, std::fma(a2, db.y, h.s * cb.y)),
+             std::fma(vpsi3, dcb.z, std::fma(a2, db.z, h.s * cb.z)));
 }
 
 // Neo-Hookean (Sec. 3.1): 2 Psi_2 = mu.

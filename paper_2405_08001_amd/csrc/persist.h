@@ -87,6 +87,19 @@ constexpr int kPersistMaxIters = 512;  // iterations of one launch (the host loo
 
 // Host-built tables of PersistArgs, and the layouts of the two element forms:
 // [0] by tet, [1] by (tet, corner) lane for the corotated models.
+// The adjoint's persistent CG kernel on the same tables.  Local vertices: x, z,
+// p, w; own ones: q, diag, lam (3 doubles each), m, fl, run; the rest as in
+// PersistLayout, with three values per slot.
+struct CgLayout {
+  unsigned x, z, p, w, q, diag, lam, m, res, tot, tl, hv, seg, run, wm, fl;
+};
+struct CgPersist {
+  PersistArgs P;
+  CgLayout at;
+  size_t lds;
+  int most;              // entries of the largest block's chunk
+};
+
 // A table that is filled after it is sized (a vector would write it twice).
 template <typename T>
 struct PersistTable {
@@ -109,7 +122,8 @@ struct PersistTables {
   PersistTable<unsigned short> dtet;
   std::vector<unsigned short> dvert;
   PersistArgs form[2];
-  bool ok[2];           // a block's share fits in LDS
+  CgPersist cg;         // layout only
+  bool ok[2], cg_ok;    // a block's share fits in LDS
 };
 inline int persist_form(int model) { return model == kModelCorot ? 1 : 0; }
 void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc, const std::vector<int>& inc_vert,

@@ -279,6 +279,34 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
 
   // the chunks' tets
   const int nc = T.form[0].chunks;
+  if (T.ok[0] && fp64) {
+    size_t o = 0;
+    auto put = [&](unsigned& f, size_t bytes, size_t align) {
+      o = (o + align - 1) / align * align;
+      f = (unsigned)o;
+      o += bytes;
+    };
+    const size_t cap_seg = cap_own + 3 * cap_w, cw = (cap_w + nc - 1) / nc;
+    CgLayout& L = T.cg.at;
+    put(L.wm, 16 * cap_w, 16);
+    put(L.x, 24 * cap_loc, 8);
+    put(L.z, 24 * cap_loc, 8);
+    put(L.p, 24 * cap_loc, 8);
+    put(L.w, 24 * cap_loc, 8);
+    put(L.q, 24 * cap_own, 8);
+    put(L.diag, 24 * cap_own, 8);
+    put(L.lam, 24 * cap_own, 8);
+    put(L.m, 8 * cap_own, 8);
+    put(L.res, 24 * cw * kWave, 8);
+    put(L.tot, 24 * cap_seg, 8);
+    put(L.tl, 8 * cap_tet, 8);
+    put(L.hv, 4 * cap_loc, 4);
+    put(L.seg, 4 * cap_seg, 4);
+    put(L.run, 4 * cap_own, 4);
+    put(L.fl, cap_own, 1);
+    T.cg.lds = o;
+    T.cg_ok = o <= kPersistLds;
+  }
   Lists<PersistEntry> entry(blocks);
   Lists<ushort2> seg(blocks);
   std::vector<int4> chunk((size_t)blocks * (nc + 1), make_int4(0, 0, 0, 0));
@@ -346,6 +374,8 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
       s0 += seg.n[p];
     }
   }
+  for (size_t i = 0; i < chunk.size(); ++i)
+    if (i % (nc + 1) != (size_t)nc) T.cg.most = std::max(T.cg.most, chunk[i + 1].x - chunk[i].x);
   T.chunk.swap(chunk);
   entry.close(T.entry);
   seg.close(T.seg);
