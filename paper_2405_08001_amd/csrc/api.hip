@@ -169,8 +169,7 @@ struct pncg_ctx {
   long long cand_cap = 0;
   // segmented scatter: the list's per-vertex entry index and the run
   // partials of its pair terms (sized by cand_cap)
-  int *d_vcnt = nullptr, *d_coff = nullptr, *d_cent = nullptr, *d_cent_tmp = nullptr, *d_pl_tmp = nullptr,
-      *d_big = nullptr;
+  int *d_vcnt = nullptr, *d_coff = nullptr, *d_cent = nullptr, *d_cent_tmp = nullptr, *d_pl_tmp = nullptr;
   unsigned long long* d_ckey_tmp = nullptr;
   int2 *d_wvert = nullptr, *d_wrange = nullptr;   // per incidence wave: first / last vertex, entry range
   double* d_rp = nullptr;      // [4 cap][6] run partials of the pair entries
@@ -201,9 +200,10 @@ struct pncg_ctx {
   double* d_scalar = nullptr;      // [8]
   // broad phase
   int tsize = 0;
-  int *d_count = nullptr, *d_start = nullptr;
+  int* d_count = nullptr;
+  int2* d_range = nullptr;
   double4 *d_item_lo = nullptr, *d_item_hi = nullptr;
-  long long *d_item_cnt = nullptr, *d_item_off = nullptr;
+  long long* d_item_off = nullptr;
   long long ent_cap = 0;
   unsigned long long* d_bkt_key = nullptr;
   int *d_bkt_item = nullptr, *d_ent_rank = nullptr;
@@ -426,7 +426,6 @@ Broad make_broad(pncg_ctx* c) {
   B.n_excl_ee = c->n_excl_ee;
   B.item_lo = c->d_item_lo;
   B.item_hi = c->d_item_hi;
-  B.item_cnt = c->d_item_cnt;
   B.item_off = c->d_item_off;
   B.shift = c->cell_shift;
   B.ent_cap = c->ent_cap;
@@ -436,9 +435,14 @@ Broad make_broad(pncg_ctx* c) {
   B.bkt_lo = c->d_bkt_lo;
   B.bkt_hi = c->d_bkt_hi;
   B.bkt_ids = c->d_bkt_ids;
-  B.tsize = c->tsize;
+  // (the grid's cells are fewer than the caller's cells that the table is sized by)
+  int ts = 1024;
+  while (ts < 8 * (c->nF + c->nE)) ts <<= 1;
+  B.tsize = std::min(c->tsize, std::max(c->tsize >> (2 * std::min(c->cell_shift, 10)), ts));
   B.count = c->d_count;
-  B.start = c->d_start;
+  B.range = c->d_range;
+  B.resv = reinterpret_cast<unsigned long long*>(c->d_totals + 8);
+  B.espan = c->d_totals + 4;
   B.work_cap = c->work_cap;
   B.part_cnt = c->d_part_cnt;
   B.part_off = c->d_part_off;
@@ -458,7 +462,7 @@ PairIndex make_pairindex(pncg_ctx* c) {
   P.cent_tmp = c->d_cent_tmp;
   P.ckey_tmp = c->d_ckey_tmp;
   P.pv = c->d_pv;
-  P.big = c->d_big;
+  P.place = reinterpret_cast<int4*>(c->d_cent);
   P.scan_tmp = c->d_pl_tmp;
   P.wvert = c->d_wvert;
   P.wrange = c->d_wrange;
@@ -537,8 +541,9 @@ int install_override(pncg_ctx* c) {
 int alloc_grid(pncg_ctx* c, long long ent) {
   int rc;
   drop_graphs(c);
-  for (void* p : {(void*)c->d_ent_rank, (void*)c->d_bkt_key, (void*)c->d_bkt_item, (void*)c->d_bkt_lo, (void*)c->d_bkt_hi, (void*)c->d_bkt_ids, (void*)c->d_count,
-                  (void*)c->d_start, (void*)c->d_part_cnt, (void*)c->d_part_off})
+  for (void* p : {(void*)c->d_ent_rank, (void*)c->d_bkt_key, (void*)c->d_bkt_item, (void*)c->d_bkt_lo,
+                  (void*)c->d_bkt_hi, (void*)c->d_bkt_ids, (void*)c->d_count, (void*)c->d_range,
+                  (void*)c->d_part_cnt, (void*)c->d_part_off})
     dfree(c, p);
   c->ent_cap = std::max<long long>(ent, 4096);
   int ts = 1024;
@@ -549,9 +554,10 @@ int alloc_grid(pncg_ctx* c, long long ent) {
       (rc = dmalloc(c, &c->d_bkt_key, c->ent_cap)) || (rc = dmalloc(c, &c->d_bkt_item, c->ent_cap)) ||
       (rc = dmalloc(c, &c->d_bkt_lo, c->ent_cap)) || (rc = dmalloc(c, &c->d_bkt_hi, c->ent_cap)) ||
       (rc = dmalloc(c, &c->d_bkt_ids, c->ent_cap)) ||
-      (rc = dmalloc(c, &c->d_count, ts)) || (rc = dmalloc(c, &c->d_start, ts + 1)) ||
+      (rc = dmalloc(c, &c->d_count, ts)) || (rc = dmalloc(c, &c->d_range, ts)) ||
       (rc = dmalloc(c, &c->d_part_cnt, c->work_cap)) || (rc = dmalloc(c, &c->d_part_off, c->work_cap + 4096)))
     return rc;
+  HIPCHK(c, hipMemsetAsync(c->d_count, 0, sizeof(int) * (size_t)ts, c->stream));
   return PNCG_OK;
 }
 
@@ -617,7 +623,6 @@ int build_solver_list(pncg_ctx* c, const double4* x) {
   auto enqueue = [&]() {
     broad_solver_list(B, x, c->cell, r, c->d_cand, c->cand_cap, c->d_ncand, &c->d_status->err,
                       &c->d_status->n_cand, c->stream, seg ? &P : nullptr, c->d_xbuild);
-    if (seg) pairs_index(P, c->d_cand, c->d_ncand, c->cand_cap, c->stream, true);
   };
   if (!c->graphs || c->noalloc) {
     enqueue();
@@ -1453,11 +1458,10 @@ int pncg_set_mesh(pncg_ctx* c, int32_t nV, const double* X, int32_t nT, const in
       (rc = dmalloc(c, &c->d_part_dir, 4 * (size_t)gmax)) || (rc = dmalloc(c, &c->d_part_narrow, gmax)) ||
       (rc = dmalloc(c, &c->d_io, 12 * (size_t)nV)) || (rc = dmalloc(c, &c->d_scalar, 8)) ||
       (rc = dmalloc(c, &c->d_item_lo, (size_t)nF + nE)) || (rc = dmalloc(c, &c->d_item_hi, (size_t)nF + nE)) ||
-      (rc = dmalloc(c, &c->d_item_cnt, (size_t)nF + nE + surf.size())) ||
-      (rc = dmalloc(c, &c->d_item_off, (size_t)nF + nE + surf.size() + 1)) ||
-      (rc = dmalloc(c, &c->d_totals, 4)) ||
-      (rc = dmalloc(c, &c->d_vcnt, 2 * (size_t)nV)) || (rc = dmalloc(c, &c->d_coff, (size_t)nV + 1)) ||
-      (rc = dmalloc(c, &c->d_pl_tmp, (size_t)nV / kTileScan + 16)) || (rc = dmalloc(c, &c->d_big, (size_t)nV + 1)) || (rc = dmalloc(c, &c->d_wvert, (size_t)c->nWaves)) ||
+      (rc = dmalloc(c, &c->d_item_off, (size_t)nF + nE)) ||
+      (rc = dmalloc(c, &c->d_totals, 16)) ||
+      (rc = dmalloc(c, &c->d_vcnt, (size_t)nV)) || (rc = dmalloc(c, &c->d_coff, (size_t)nV + 1)) ||
+      (rc = dmalloc(c, &c->d_pl_tmp, (size_t)nV / kTileScan + 16)) || (rc = dmalloc(c, &c->d_wvert, (size_t)c->nWaves)) ||
       (rc = dmalloc(c, &c->d_wrange, (size_t)c->nWaves)))
     return rc;
   {
@@ -1481,12 +1485,13 @@ int pncg_set_mesh(pncg_ctx* c, int32_t nV, const double* X, int32_t nT, const in
   c->d_bkt_key = nullptr; c->d_bkt_item = nullptr;
   c->d_ent_rank = nullptr;
   c->d_bkt_lo = nullptr; c->d_bkt_hi = nullptr; c->d_bkt_ids = nullptr;
-  c->d_count = nullptr; c->d_start = nullptr; c->d_part_cnt = nullptr; c->d_part_off = nullptr;
+  c->d_count = nullptr; c->d_range = nullptr; c->d_part_cnt = nullptr; c->d_part_off = nullptr;
   // grid entries: start with eight cells per primitive; grown on demand
   if ((rc = alloc_grid(c, 8LL * (nF + nE) + (long long)surf.size() + 4096))) return rc;
   // the solver list's first capacity, so that steps start without allocating
   if ((rc = ensure_cand_cap(c, std::max<long long>(4096, 2LL * (long long)surf.size())))) return rc;
   HIPCHK(c, hipMemsetAsync(c->d_ncand, 0, 4 * sizeof(long long), c->stream));
+  HIPCHK(c, hipMemsetAsync(c->d_totals, 0, 16 * sizeof(long long), c->stream));
   HIPCHK(c, hipMemcpyAsync(c->d_inc, inc.data(), sizeof(int) * inc.size(), hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipMemcpyAsync(c->d_inc_vert, incv.data(), sizeof(int) * incv.size(), hipMemcpyHostToDevice, c->stream));
   if (nF) HIPCHK(c, hipMemcpyAsync(c->d_tris, tris, sizeof(int) * 3 * (size_t)nF, hipMemcpyHostToDevice, c->stream));

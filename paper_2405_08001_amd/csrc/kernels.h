@@ -38,8 +38,7 @@ struct Broad {
   // items 0..nF-1 triangles, nF.. edges
   double4* item_lo;      // [nF + nE] triangle: min - r; edge: min
   double4* item_hi;      // [nF + nE] triangle: max + r; edge: max
-  long long* item_cnt;   // [nF + nE + nSV] caller's cells touched (primitives, then vertices)
-  long long* item_off;   // [nF + nE + nSV + 1]
+  long long* item_off;   // [nF + nE] first entry of the item
   int shift;             // a cell of the grid is 2^shift caller's cells to a side
   // cell entries, grouped by hash bucket
   long long ent_cap;             // counted in caller's cells
@@ -50,8 +49,11 @@ struct Broad {
   double4* bkt_hi;               // [ent_cap]
   int4* bkt_ids;                 // [ent_cap] vertex ids of the item (-1 unused)
   int tsize;             // power of two
-  int* count;            // [tsize]
-  int* start;            // [tsize + 1]
+  int* count;            // [tsize] entries of the buckets while they are counted, 0 between builds
+  int2* range;           // [tsize] slots [x, y) of the buckets; edges' are the last
+  unsigned long long* resv;   // [3] reserved so far: entries (caller's cells), triangle slots, edge slots; 0 between
+                              // builds
+  long long* espan;      // [2] slots of the edge buckets
   // pair counting: PT and EE counts per entry
   long long work_cap;    // = 2 * ent_cap
   long long* part_cnt;   // [work_cap]
@@ -76,9 +78,8 @@ void broad_fill(const Broad& B, const double4* x, double cell, double r, double 
 // (v, f) point-triangle, (e1, ~e2) edge-edge; ncand[0] = pairs found,
 // ncand[1] = -1).  Sets kErrCapacity in *err if the grid entries or the
 // pairs exceeded their capacity (the list is then incomplete), and copies
-// the pair count to *n_out.  With P its launch also zeroes the pair index's
-// counters (pairs_index is then called with zeroed = true), and with xbuild
-// it copies x there (the list's build positions).
+// the pair count to *n_out.  With P it also builds the pair index, and with
+// xbuild it copies x there (the list's build positions).
 struct PairIndex;
 void broad_solver_list(const Broad& B, const double4* x, double cell, double r, int2* out, long long cap,
                        long long* ncand, int* err, long long* n_out, hipStream_t s, const PairIndex* P = nullptr,
@@ -89,7 +90,9 @@ struct PairIndex {
   int nV;
   const int* tris;       // [nF][3]
   const int* edges;      // [nE][2]
-  int* vcnt;             // [2 nV] entries per vertex, then fill counters
+  int* vcnt;             // [nV] entries per vertex
+  int4* place;           // [cap] place of each corner of pair q among its vertex's entries as they came (in cent,
+                         // which is written last)
   int* coff;             // [nV + 1] their offsets
   int* cent;             // [4 cap] slot ids (4 q + corner) grouped by vertex, each vertex's in the
                          // order of its pairs' (kind, first index, second index)
@@ -97,7 +100,6 @@ struct PairIndex {
   unsigned long long* ckey_tmp;  // [4 cap] the pair key of each entry of cent_tmp
   int4* pv;              // [cap] the four vertices of pair q in narrow-phase order; edge-edge
                          // pairs store ~v3 in w (the kind is the sign of w)
-  int* big;              // [nV + 1] vertices with more entries than a thread orders ([0] = count)
   int* scan_tmp;         // scan partials, nV / 4096 + 2 ints
   // entry range [x, y) of each 64-lane wave of the vertex incidence (its
   // vertices' entries), so that waves without entries skip the pair sums
@@ -111,7 +113,7 @@ struct PairIndex {
 // range.  The entry order depends on the set of pairs only, not on their
 // order in the list.  No host synchronisation; deterministic.
 void pairs_index(const PairIndex& P, const int2* list, const long long* ncand, long long cap, hipStream_t s,
-                 bool zeroed = false);
+                 bool entered = false, const Broad* B = nullptr, int* err = nullptr, long long* n_out = nullptr);
 // Copy n pairs (kind in the pair) into out, set ncand = {n, -1} and *n_out = n.
 // dst[v] = src[v] for v < n (the list's build positions).
 void copy_positions(double4* dst, const double4* src, int n, hipStream_t s);
