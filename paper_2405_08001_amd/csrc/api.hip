@@ -966,6 +966,37 @@ int query_candidates(pncg_ctx* c, double r) {
   return build_candidates(c, c->d_x0, r, r, 0, nullptr, nullptr, true);
 }
 
+// The list of a gradient or Hessian-vector query at d_x0 under the segmented
+// scatter: the solver's list (pairs by distance, one emission pass) within
+// dhat, a little wider so that both sides of the barrier's support round
+// alike.  Its terms are summed in the index's order, so the order of the
+// emission does not show.  The counting form makes every test twice and takes
+// two more host round trips: 280 us against 150 at a packed pile of 110,000
+// tets.
+int query_pairs(pncg_ctx* c) {
+  if (!self_contact(c) || c->ovr_set[0] || c->ovr_set[1] || c->scatter != PNCG_SCATTER_SEGMENTED)
+    return query_candidates(c, c->dhat);
+  int rc;
+  c->list_valid = false;
+  if ((rc = ensure_cand_cap(c, std::max<long long>(4096, 2LL * c->nSV)))) return rc;
+  long long cnt[2] = {0, 0};
+  for (int attempt = 0;; ++attempt) {
+    const PairIndex P = make_pairindex(c);
+    // (capacities are checked here: not through the status)
+    broad_solver_list(make_broad(c), c->d_x0, c->cell, c->dhat * (1.0 + 1e-9), c->d_cand, c->cand_cap, c->d_ncand,
+                      reinterpret_cast<int*>(c->d_totals + 12), c->d_totals + 13, c->stream, &P);
+    HIPCHK(c, hipMemcpyAsync(c->h_n, c->d_totals, sizeof(long long), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->h_n + 1, c->d_ncand, sizeof(long long), hipMemcpyDeviceToHost, c->stream));
+    if ((rc = sync(c))) return rc;
+    cnt[0] = c->h_n[0];
+    cnt[1] = c->h_n[1];
+    if (cnt[0] <= c->ent_cap && cnt[1] <= c->cand_cap) return PNCG_OK;
+    if (attempt == 2) return fail(c, PNCG_E_NOMEM, "spatial grid did not fit");
+    if (cnt[0] > c->ent_cap && (rc = alloc_grid(c, cnt[0] + cnt[0] / 4))) return rc;
+    if (cnt[1] > c->cand_cap && (rc = ensure_cand_cap(c, std::max<long long>(cnt[1] + cnt[1] / 2, 1024)))) return rc;
+  }
+}
+
 int stage_positions(pncg_ctx* c, const double* x) {
   if (!finite_all(x, 3 * (size_t)c->nV)) return fail(c, PNCG_E_NONFINITE, "non-finite position");
   int rc = upload_rows(c, x, c->d_io, c->nV);
@@ -975,7 +1006,7 @@ int stage_positions(pncg_ctx* c, const double* x) {
 }
 
 template <typename R>
-int load_query(pncg_ctx* c, const double* x, const double* xt, const double* p) {
+int load_query(pncg_ctx* c, const double* x, const double* xt, const double* p, bool indexed) {
   const size_t n3 = 3 * (size_t)c->nV;
   if (!finite_all(x, n3) || (xt && !finite_all(xt, n3)) || (p && !finite_all(p, n3)))
     return fail(c, PNCG_E_NONFINITE, "non-finite input");
@@ -985,7 +1016,7 @@ int load_query(pncg_ctx* c, const double* x, const double* xt, const double* p) 
   if (p && (rc = upload_rows(c, p, c->d_io + 2 * n3, c->nV))) return rc;
   Args<R> A = make_args<R>(c, 1.0);
   launch_load_query<R>(A, c->d_io, xt ? c->d_io + n3 : nullptr, p ? c->d_io + 2 * n3 : nullptr, c->stream);
-  return query_candidates(c, c->dhat);
+  return indexed ? query_pairs(c) : query_candidates(c, c->dhat);
 }
 
 int finish_query(pncg_ctx* c) {
@@ -996,7 +1027,7 @@ int finish_query(pncg_ctx* c) {
 
 template <typename R>
 int energy_impl(pncg_ctx* c, const double* x, const double* xt, double h, double* out) {
-  int rc = load_query<R>(c, x, xt, nullptr);
+  int rc = load_query<R>(c, x, xt, nullptr, false);
   if (rc) return rc;
   Args<R> A = make_args<R>(c, h);
   if ((rc = list_args(c, A))) return rc;
@@ -1007,7 +1038,7 @@ int energy_impl(pncg_ctx* c, const double* x, const double* xt, double h, double
 
 template <typename R>
 int gradient_impl(pncg_ctx* c, const double* x, const double* xt, double h, double* g, double* d) {
-  int rc = load_query<R>(c, x, xt, nullptr);
+  int rc = load_query<R>(c, x, xt, nullptr, true);
   if (rc) return rc;
   Args<R> A = make_args<R>(c, h);
   if ((rc = list_args(c, A))) return rc;
@@ -1022,7 +1053,7 @@ int gradient_impl(pncg_ctx* c, const double* x, const double* xt, double h, doub
 
 template <typename R>
 int hvp_impl(pncg_ctx* c, const double* x, const double* p, double h, double* hp, double* php) {
-  int rc = load_query<R>(c, x, nullptr, p);
+  int rc = load_query<R>(c, x, nullptr, p, true);
   if (rc) return rc;
   Args<R> A = make_args<R>(c, h);
   if ((rc = list_args(c, A))) return rc;
