@@ -78,6 +78,12 @@ template <typename R, int BS, bool LDSX, int M>
 __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double* x_in, const double* v_in,
                                                    double* x_out, double* v_out) {
   constexpr int NW = BS / kWave;
+  // At 512 threads one workgroup fills a compute unit's registers with or
+  // without the prefetches (160 to 180 of them, 200 to 250 with), so two waves per SIMD
+  // have nothing else to hide the round trips of the records and codes with
+  // (256 scenes of 500 to 8,000 tets, mixed: 5.55 -> 4.66 ms).  At 256 they would
+  // cost the third workgroup; at 1024, and in the float64 corotated form, they spill.
+  constexpr bool PRE = BS == 512 && !(M == kModelCorot && sizeof(R) == sizeof(double));
   __shared__ double sh[NW * 8];
   extern __shared__ double dyn[];
   double* sx = dyn;                                  // [3][vcap]
@@ -136,13 +142,52 @@ __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double*
     for (;;) {
       // ---- gradient, diag(H), dot products (vertex-centric sweep)
       double dots[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      // (PRE: the record of the next wave of lanes and the codes of the one
+      // after are on their way meanwhile, and the vertex arrays while the
+      // element terms are formed)
+      [[maybe_unused]] int code1 = -1, myv1 = -1, code2 = -1, myv2 = -1;
+      [[maybe_unused]] ElemRec<R> rec1;
+      if constexpr (PRE) {
+        const int w = w0 + r * NW + wave;
+        if (w < w1) {
+          code1 = A.inc[w * kWave + lane];
+          myv1 = A.inc_vert[w * kWave + lane];
+        }
+        if (w + G * NW < w1) {
+          code2 = A.inc[(w + G * NW) * kWave + lane];
+          myv2 = A.inc_vert[(w + G * NW) * kWave + lane];
+        }
+        if (code1 >= 0) rec1 = A.elem[code1 >> 2];
+      }
       for (int w = w0 + r * NW + wave; w < w1; w += G * NW) {
         const int idx = w * kWave + lane;
-        const int code = A.inc[idx];
-        const int myv = A.inc_vert[idx];
+        const int code = PRE ? code1 : A.inc[idx];
+        const int myv = PRE ? myv1 : A.inc_vert[idx];
+        [[maybe_unused]] ElemRec<R> rec0;
+        [[maybe_unused]] V3<double> xt0;
+        [[maybe_unused]] V3<R> gp0;
+        [[maybe_unused]] double m0;
+        [[maybe_unused]] uint8_t fl0;
+        if constexpr (PRE) {
+          rec0 = rec1;
+          if (myv >= 0) {
+            xt0 = ld3(A.xt, myv);
+            m0 = A.mass[myv];
+            fl0 = A.vflag[myv];
+            gp0 = ldr<R>(A.g, myv);
+          }
+          code1 = code2;
+          myv1 = myv2;
+          code2 = myv2 = -1;
+          if (code1 >= 0) rec1 = A.elem[code1 >> 2];
+          if (w + 2 * G * NW < w1) {
+            code2 = A.inc[idx + 2 * G * NW * kWave];
+            myv2 = A.inc_vert[idx + 2 * G * NW * kWave];
+          }
+        }
         R sv[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
         if (code >= 0) {
-          const ElemRec<R> rec = A.elem[code >> 2];
+          const ElemRec<R> rec = PRE ? rec0 : A.elem[code >> 2];
           Kin<R> kin = kinematics<R>(rec.B, X(rec.v[0]), X(rec.v[1]), X(rec.v[2]), X(rec.v[3]));
           V3<R> g, dg;
           bool ok;
@@ -162,12 +207,12 @@ __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double*
         }
         if (!seg_sum_shfl(myv, sv) || myv < 0) continue;
         const int v = myv;
-        const V3<double> x = X(v), xt = ld3(A.xt, v);
-        const double m = A.mass[v];
+        const V3<double> x = X(v), xt = PRE ? xt0 : ld3(A.xt, v);
+        const double m = PRE ? m0 : A.mass[v];
         double gd[3] = {A.h2 * double(sv[0]) + m * (x.x - xt.x), A.h2 * double(sv[1]) + m * (x.y - xt.y),
                         A.h2 * double(sv[2]) + m * (x.z - xt.z)};
         double dd[3] = {A.h2 * double(sv[3]) + m, A.h2 * double(sv[4]) + m, A.h2 * double(sv[5]) + m};
-        if (has_plane && (A.vflag[v] & kSurface)) {
+        if (has_plane && ((PRE ? fl0 : A.vflag[v]) & kSurface)) {
           const double d = plane_dist(pl, x);
           if (d < A.dhat) {
             if (!(d > 0.0)) {
@@ -183,7 +228,7 @@ __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double*
         }
         const V3<R> gR = mk3(R(gd[0]), R(gd[1]), R(gd[2]));
         const V3<R> pgR = mk3(R(gd[0] / dd[0]), R(gd[1] / dd[1]), R(gd[2] / dd[2]));
-        const V3<R> gpR = ldr<R>(A.g, v), ppR = Pd(v);
+        const V3<R> gpR = PRE ? gp0 : ldr<R>(A.g, v), ppR = Pd(v);
         str<R>(A.g, v, gR);
         str<R>(A.pg, v, pgR);
         const double g3[3] = {double(gR.x), double(gR.y), double(gR.z)};
@@ -240,8 +285,11 @@ __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double*
       __syncthreads();
       // ---- element p^T H p
       double el = 0.0;
+      [[maybe_unused]] ElemRec<R> tet1;
+      if (PRE && t0 + r * BS + tid < t1) tet1 = A.elem[t0 + r * BS + tid];
       for (int e = t0 + r * BS + tid; e < t1; e += G * BS) {
-        const ElemRec<R> rec = A.elem[e];
+        const ElemRec<R> rec = PRE ? tet1 : A.elem[e];
+        if (PRE && e + G * BS < t1) tet1 = A.elem[e + G * BS];
         Kin<R> kin = kinematics<R>(rec.B, X(rec.v[0]), X(rec.v[1]), X(rec.v[2]), X(rec.v[3]));
         V3<R> d[3];
         dF_cols(rec.B, Pd(rec.v[0]), Pd(rec.v[1]), Pd(rec.v[2]), Pd(rec.v[3]), d);
