@@ -12,25 +12,68 @@
 
 namespace pncg {
 
+// The members' partial sums, and in scenes of up to kWordVerts vertices P g,
+// go by agent-scope words, which pass the caches: such a meeting needs no
+// agent-scope fence, which writes back and invalidates the L2 that the XCD's
+// other workgroups find their records in.  P g of larger scenes is read by all
+// members from the L2 after one fence per iteration.  Per step of 40
+// iterations, with a fence at the first meeting / by words throughout (both
+// meetings fenced before: 1.7 ms for the first):
+//   42 scenes of 207 to 700 tets, mixed           1256 /  951 us
+//   100 of 300 to 2,000, mixed                    1752 / 1498
+//   256 of 500 to 8,000, mixed (50 iterations)    4636 / 4731
+constexpr int kWordVerts = 512;
+typedef unsigned long long u64;
+__device__ __forceinline__ u64 ld_agent(const u64* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_agent(u64* p, u64 v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st3_agent(double4* a, int v, V3<double> q) {
+  u64* p = reinterpret_cast<u64*>(a + v);
+  st_agent(p, (u64)__double_as_longlong(q.x));
+  st_agent(p + 1, (u64)__double_as_longlong(q.y));
+  st_agent(p + 2, (u64)__double_as_longlong(q.z));
+}
+__device__ __forceinline__ void st3_agent(float4* a, int v, V3<float> q) {
+  u64* p = reinterpret_cast<u64*>(a + v);
+  st_agent(p, (u64)(unsigned)__float_as_int(q.x) | ((u64)(unsigned)__float_as_int(q.y) << 32));
+  st_agent(p + 1, (u64)(unsigned)__float_as_int(q.z));
+}
+__device__ __forceinline__ V3<double> ld3_agent(const double4* a, int v) {
+  const u64* p = reinterpret_cast<const u64*>(a + v);
+  const u64 x = ld_agent(p), y = ld_agent(p + 1), z = ld_agent(p + 2);
+  return mk3(__longlong_as_double((long long)x), __longlong_as_double((long long)y), __longlong_as_double((long long)z));
+}
+__device__ __forceinline__ V3<float> ld3_agent(const float4* a, int v) {
+  const u64* p = reinterpret_cast<const u64*>(a + v);
+  const u64 w = ld_agent(p), z = ld_agent(p + 1);
+  return mk3(__int_as_float((int)(unsigned)w), __int_as_float((int)(unsigned)(w >> 32)), __int_as_float((int)(unsigned)z));
+}
+
 // Barrier among the workgroups of one team, waited on by one thread with a
-// bounded number of polls.  The agent-scope fences publish this workgroup's
-// stores before it arrives and make the others' visible after.  A wait that
-// runs out of polls raises kErrTeam, and once that bit is set every later
-// team barrier of the launch passes at once, so the launch always ends.
+// bounded number of polls.  FENCE: agent-scope fences publish all of this
+// workgroup's stores before it arrives and make the others' visible after;
+// otherwise that holds for agent-scope words only.  A wait that runs out of
+// polls raises kErrTeam, and once that bit is set every later team barrier of
+// the launch passes at once, so the launch always ends.
+template <bool FENCE>
 __device__ __forceinline__ void team_sync(int* bar, int target, int* err, int limit) {
+  if constexpr (!FENCE) __builtin_amdgcn_s_waitcnt(0);   // the words have arrived
   __syncthreads();
   if (threadIdx.x == 0) {
-    __threadfence();
-    atomicAdd(bar, 1);
+    if constexpr (FENCE) __threadfence();
+    __hip_atomic_fetch_add(bar, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int polls = 0;
     while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
       if (++polls > limit || (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrTeam)) {
         atomicOr(err, kErrTeam);
         break;
       }
-      __builtin_amdgcn_s_sleep(2);
+      __builtin_amdgcn_s_sleep(1);
     }
-    __threadfence();
+    if constexpr (FENCE) __threadfence();
   }
   __syncthreads();
 }
@@ -44,22 +87,35 @@ struct Team {
   int* err;
   int limit;
   __device__ void sync() {
-    if (G > 1) team_sync(bar, G * ++nb, err, limit);
+    if (G > 1) team_sync<true>(bar, G * ++nb, err, limit);
   }
   // Block reduction, then (G > 1) the members' results combined in rank
   // order, so every member holds the same bits.
   template <int N, int BS>
-  __device__ void reduce(double (&v)[N], const int (&kind)[N], double* sh) {
+  __device__ void reduce(double (&v)[N], const int (&kind)[N], double* sh, bool fence) {
     block_reduce<N, BS>(v, kind, sh);
     if (G == 1) return;
-    double* slot = part + ((nb + 1) & 1) * (kMaxTeam * 8);
+    u64* slot = reinterpret_cast<u64*>(part + ((nb + 1) & 1) * (kMaxTeam * 8));
     if (threadIdx.x == 0)
-      for (int i = 0; i < N; ++i) slot[r * 8 + i] = v[i];
-    sync();
-    for (int i = 0; i < N; ++i) {
-      double acc = slot[i];
-      for (int j = 1; j < G; ++j) acc = kind[i] ? fmax(acc, slot[j * 8 + i]) : acc + slot[j * 8 + i];
-      v[i] = acc;
+      for (int i = 0; i < N; ++i) st_agent(slot + r * 8 + i, (u64)__double_as_longlong(v[i]));
+    if (fence) team_sync<true>(bar, G * ++nb, err, limit);
+    else team_sync<false>(bar, G * ++nb, err, limit);
+    // the members' results in rank order, by way of LDS where all fit in it
+    auto total = [&](auto&& word) {
+      for (int i = 0; i < N; ++i) {
+        double acc = word(i);
+        for (int j = 1; j < G; ++j) acc = kind[i] ? fmax(acc, word(j * 8 + i)) : acc + word(j * 8 + i);
+        v[i] = acc;
+      }
+    };
+    auto load = [&](int i) { return __longlong_as_double((long long)ld_agent(slot + i)); };
+    if constexpr (BS / kWave >= kMaxTeam) {
+      if (threadIdx.x < (unsigned)(8 * G)) sh[threadIdx.x] = load(threadIdx.x);
+      __syncthreads();
+      total([&](int i) { return sh[i]; });
+      __syncthreads();
+    } else {
+      total(load);
     }
   }
 };
@@ -101,6 +157,7 @@ __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double*
     const int w0 = A.wave_off[s], w1 = A.wave_off[s + 1];
     const double* pl = A.planes + 4 * s;
     const bool has_plane = pl[0] != 0.0 || pl[1] != 0.0 || pl[2] != 0.0;
+    const bool words = LDSX && G > 1 && v1 - v0 <= kWordVerts;   // P g between the members
     auto X = [&](int v) -> V3<double> {
       if (!LDSX) return ld3(A.x, v);
       const int l = v - v0;
@@ -230,7 +287,8 @@ __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double*
         const V3<R> pgR = mk3(R(gd[0] / dd[0]), R(gd[1] / dd[1]), R(gd[2] / dd[2]));
         const V3<R> gpR = PRE ? gp0 : ldr<R>(A.g, v), ppR = Pd(v);
         str<R>(A.g, v, gR);
-        str<R>(A.pg, v, pgR);
+        if (words) st3_agent(A.pg, v, pgR);
+        else str<R>(A.pg, v, pgR);
         const double g3[3] = {double(gR.x), double(gR.y), double(gR.z)};
         const double pg3[3] = {double(pgR.x), double(pgR.y), double(pgR.z)};
         const double gp3[3] = {double(gpR.x), double(gpR.y), double(gpR.z)};
@@ -247,7 +305,7 @@ __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double*
       }
       {
         const int kind[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        T.reduce<8, BS>(dots, kind, sh);
+        T.reduce<8, BS>(dots, kind, sh, !words);
       }
       const double gnorm = sqrt(dots[0]);
       if (k == 0) g0 = gnorm;
@@ -267,7 +325,7 @@ __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double*
       const R rb = R(beta);
       double php = 0.0, pmv = 0.0, pmc = 0.0;
       for (int v = v0 + tid; v < v1; v += BS) {
-        const V3<R> p = direction(ldr<R>(A.pg, v), Pd(v), rb);
+        const V3<R> p = direction(words ? ld3_agent(A.pg, v) : ldr<R>(A.pg, v), Pd(v), rb);
         setP(v, p);
         const double px = p.x, py = p.y, pz = p.z, p2 = px * px + py * py + pz * pz;
         php += A.mass[v] * p2;
@@ -304,7 +362,7 @@ __global__ void __launch_bounds__(BS) k_batch_step(BatchArgs<R> A, const double*
       double red[3] = {php + A.h2 * el, pmv, pmc};
       {
         const int kind[3] = {0, 1, 1};
-        T.reduce<3, BS>(red, kind, sh);
+        T.reduce<3, BS>(red, kind, sh, false);
       }
       const double pHp = red[0];
       const double pm = (A.flags & 2u) ? red[2] : red[1];
