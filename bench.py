@@ -83,7 +83,7 @@ KERNEL_NAMES = {"grad": "k_grad<float, 0, false, 0, true,", "dir": "k_dir<float,
                 "narrow": "k_narrow<float, false>"}
 KERNEL_TIMES = os.path.join(ROOT, "profiles", "kernel_times.json")
 CALIB_BYTES = 256 << 20          # the calibration copy reads and writes this many bytes
-SOLVER_SOURCES = ("solver_kernels.hip", "sweep_common.h", "device_math.h", "internal.h")
+SOLVER_SOURCES = ("solver_kernels.hip", "iteration_common.h", "sweep_common.h", "device_math.h", "internal.h")
 
 
 def solver_source_hash():
