@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <climits>
 #include <mutex>
+#include <new>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -1282,8 +1283,12 @@ static int setup_persist(pncg_ctx* c) {
   for (auto& m : c->cg_persist_fit) m = -1;
   for (auto& m : c->persist_fit) m[0] = m[1] = -1;
   PersistTables T;
-  persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, c->precision == PNCG_FP64,
-                c->nF + c->nE > 0, T);
+  try {
+    persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, c->precision == PNCG_FP64,
+                  c->nF + c->nE > 0, T);
+  } catch (const std::bad_alloc&) {
+    return PNCG_OK;   // no memory for the tables: the iterations are launched
+  }
   if (!T.ok[0] && !T.ok[1]) return PNCG_OK;
   std::vector<uint8_t> fl(c->vflag);
   for (int i : c->tris) fl[i] |= kPairVertex;

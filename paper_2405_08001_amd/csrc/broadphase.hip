@@ -247,9 +247,10 @@ __global__ void __launch_bounds__(kItemBlock) k_items(Broad B, const double4* x,
       B.item_lo[i] = make_double4(lo.x, lo.y, lo.z, 0.0);
       B.item_hi[i] = make_double4(hi.x, hi.y, hi.z, 0.0);
       cull_box(B, i, r, lo, hi, cl, ch);
-      cnt = cells_between(cell_of(cl, inv, 0), cell_of(ch, inv, 0));
+      // entries are counted in caller's cells, up to a bound that no capacity
+      // reaches and whose sums cannot overflow
+      cnt = min(cells_between(cell_of(cl, inv, 0), cell_of(ch, inv, 0)), 1ll << 40);
     }
-    // entries are counted in caller's cells
     incl = cnt;
     for (int o = 1; o < kWave; o <<= 1) {
       const long long u = __shfl_up(incl, o, kWave);
@@ -286,6 +287,10 @@ __global__ void __launch_bounds__(kItemBlock) k_items(Broad B, const double4* x,
   }
 }
 
+// the slot after the last (slots are ints; a capacity beyond them counts
+// caller's cells, not entries)
+__device__ __forceinline__ int slot_end(const Broad& B) { return (int)min(B.ent_cap, (long long)INT_MAX); }
+
 // Slots of the buckets: those of a tile of buckets are consecutive, and the
 // tiles follow each other as their blocks come, triangles' from the first slot
 // on, edges' up to the last.  Also empties the counters for the next build.
@@ -304,7 +309,7 @@ __global__ void __launch_bounds__(kBlock) k_bucket_alloc(Broad B, int tile) {
   if (threadIdx.x == 0) {
     const bool edge = h0 >= (B.tsize >> 1);
     const int before = (int)atomicAdd(B.resv + (edge ? 2 : 1), (unsigned long long)total);
-    sbase = edge ? (int)B.ent_cap - before - total : before;
+    sbase = edge ? slot_end(B) - before - total : before;
   }
   __syncthreads();
   at += sbase;
@@ -328,8 +333,8 @@ __global__ void __launch_bounds__(kBlock) k_bucket_fill(Broad B, const double4* 
   const int tid = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
   if (tid == 0) {
     B.totals[0] = (long long)B.resv[0];
-    B.espan[0] = B.ent_cap - (long long)B.resv[2];
-    B.espan[1] = B.ent_cap;
+    B.espan[0] = slot_end(B) - (long long)B.resv[2];
+    B.espan[1] = slot_end(B);
     for (int j = 0; j < 3; ++j) B.resv[j] = 0;
   }
   if (vcnt)

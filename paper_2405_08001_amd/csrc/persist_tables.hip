@@ -317,6 +317,7 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
     }
     entry.open();
     seg.open();
+    for (Marks& m : marks) m.entry.resize(cap_tet);
     for_blocks(blocks, workers, [&](int wk, int p) {
       Marks& K = marks[wk];
       const PersistBlock& B = T.blk[p];
@@ -325,7 +326,7 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
       int4* ch = &chunk[(size_t)p * (nc + 1)];
       const int cw = (B.nw + nc - 1) / nc;
       int own = 0, ne = 0, ns = 0;
-      K.entry.assign(B.ntet, -1);
+      std::fill(K.entry.begin(), K.entry.begin() + B.ntet, -1);
       for (int c = 0; c < nc; ++c) {
         const int wb = std::min(c * cw, B.nw), we = std::min(wb + cw, B.nw);
         const size_t i0 = (size_t)(B.w0 + wb) * kWave, i1 = (size_t)(B.w0 + we) * kWave;
