@@ -63,35 +63,51 @@ struct Closest {
   double d;
 };
 
+// a.b and a b - c d of the closest points.  FUSED: with the fused operations
+// written out, as the compiler chooses them in the per-iteration launches (in
+// a kernel of another shape it may take the products in the other order, one
+// unit in the last place away).
+template <bool FUSED>
+__device__ __forceinline__ double cdot(V3<double> a, V3<double> b) {
+  if constexpr (FUSED) return fma(a.z, b.z, fma(a.x, b.x, a.y * b.y));
+  else return dot(a, b);
+}
+template <bool FUSED>
+__device__ __forceinline__ double mdiff(double a, double b, double c, double d) {
+  if constexpr (FUSED) return fma(a, b, -(c * d));
+  else return a * b - c * d;
+}
+
 // Point x0 against triangle (x1, x2, x3): barycentric region tests on the
 // dot products of the edge vectors with the point offsets (the Voronoi
 // region method of Ericson, Real-Time Collision Detection, 2005, Sec. 5.1.5).
+template <bool FUSED = false>
 __device__ __forceinline__ Closest closest_pt(V3<double> x0, V3<double> x1, V3<double> x2, V3<double> x3) {
   V3<double> ab = x2 - x1, ac = x3 - x1, ap = x0 - x1;
-  double d1 = dot(ab, ap), d2 = dot(ac, ap);
+  double d1 = cdot<FUSED>(ab, ap), d2 = cdot<FUSED>(ac, ap);
   double v, w;  // weights of x2 and x3; x1 gets 1 - v - w
   if (d1 <= 0.0 && d2 <= 0.0) {
     v = 0.0; w = 0.0;
   } else {
     V3<double> bp = x0 - x2;
-    double d3 = dot(ab, bp), d4 = dot(ac, bp);
+    double d3 = cdot<FUSED>(ab, bp), d4 = cdot<FUSED>(ac, bp);
     if (d3 >= 0.0 && d4 <= d3) {
       v = 1.0; w = 0.0;
     } else {
-      double vc = d1 * d4 - d3 * d2;
+      double vc = mdiff<FUSED>(d1, d4, d3, d2);
       if (vc <= 0.0 && d1 >= 0.0 && d3 <= 0.0) {
         v = d1 / (d1 - d3); w = 0.0;
       } else {
         V3<double> cp = x0 - x3;
-        double d5 = dot(ab, cp), d6 = dot(ac, cp);
+        double d5 = cdot<FUSED>(ab, cp), d6 = cdot<FUSED>(ac, cp);
         if (d6 >= 0.0 && d5 <= d6) {
           v = 0.0; w = 1.0;
         } else {
-          double vb = d5 * d2 - d1 * d6;
+          double vb = mdiff<FUSED>(d5, d2, d1, d6);
           if (vb <= 0.0 && d2 >= 0.0 && d6 <= 0.0) {
             v = 0.0; w = d2 / (d2 - d6);
           } else {
-            double va = d3 * d6 - d5 * d4;
+            double va = mdiff<FUSED>(d3, d6, d5, d4);
             if (va <= 0.0 && (d4 - d3) >= 0.0 && (d5 - d6) >= 0.0) {
               w = (d4 - d3) / ((d4 - d3) + (d5 - d6));
               v = 1.0 - w;
@@ -112,7 +128,7 @@ __device__ __forceinline__ Closest closest_pt(V3<double> x0, V3<double> x1, V3<d
   r.c[3] = -w;
   r.t = ap - v * ab;
   r.t = r.t - w * ac;
-  r.d = sqrt(dot(r.t, r.t));
+  r.d = sqrt(cdot<FUSED>(r.t, r.t));
   return r;
 }
 
@@ -121,13 +137,14 @@ __device__ __forceinline__ Closest closest_pt(V3<double> x0, V3<double> x1, V3<d
 // clamped; u from s; if u leaves [0,1] it is clamped and s recomputed.
 // Parallel edges ((d1.d1)(d2.d2) - (d1.d2)^2 <= 1e-12 (d1.d1)(d2.d2)) start
 // from s = 0.
+template <bool FUSED = false>
 __device__ __forceinline__ Closest closest_ee(V3<double> x0, V3<double> x1, V3<double> x2, V3<double> x3) {
   V3<double> d1 = x1 - x0, d2 = x3 - x2, r = x0 - x2;
-  double a = dot(d1, d1), e = dot(d2, d2), f = dot(d2, r);
-  double c = dot(d1, r), b = dot(d1, d2);
-  double den = a * e - b * b;
+  double a = cdot<FUSED>(d1, d1), e = cdot<FUSED>(d2, d2), f = cdot<FUSED>(d2, r);
+  double c = cdot<FUSED>(d1, r), b = cdot<FUSED>(d1, d2);
+  double den = mdiff<FUSED>(a, e, b, b);
   double s = 0.0, u;
-  if (den > 1e-12 * a * e) s = fmin(fmax((b * f - c * e) / den, 0.0), 1.0);
+  if (den > 1e-12 * a * e) s = fmin(fmax(mdiff<FUSED>(b, f, c, e) / den, 0.0), 1.0);
   u = (b * s + f) / e;
   if (u < 0.0) {
     u = 0.0;
@@ -143,7 +160,7 @@ __device__ __forceinline__ Closest closest_ee(V3<double> x0, V3<double> x1, V3<d
   out.c[3] = -u;
   out.t = r + s * d1;
   out.t = out.t - u * d2;
-  out.d = sqrt(dot(out.t, out.t));
+  out.d = sqrt(cdot<FUSED>(out.t, out.t));
   return out;
 }
 

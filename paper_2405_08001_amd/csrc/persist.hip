@@ -147,7 +147,7 @@ __device__ __forceinline__ bool pair_at(const Args<R>& A, bool pt, const int (&i
   V3<double> X[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) X[i] = pos(iv[i]);
-  c = pt ? closest_pt(X[0], X[1], X[2], X[3]) : closest_ee(X[0], X[1], X[2], X[3]);
+  c = pt ? closest_pt<true>(X[0], X[1], X[2], X[3]) : closest_ee<true>(X[0], X[1], X[2], X[3]);
   if (!(c.d > 0.0)) {
     raise_err(A.status, kErrPenetration);
     return false;
@@ -965,8 +965,8 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
               const double c[4] = {g->c[0], g->c[1], g->c[2], g->c[3]};
               V3<double> sp;
               if (!pair_dir<R>(iv, c, src, pk, rb, limit, sp)) run.bad = 1;
-              const double st = dot(sp, mk3(g->t[0], g->t[1], g->t[2]));
-              acc_pHp += g->ca * st * st + g->cb * dot(sp, sp);
+              const double st = fdot(sp, mk3(g->t[0], g->t[1], g->t[2]));
+              acc_pHp += fma(g->cb, fdot(sp, sp), g->ca * st * st);
             }
           }
         } else {
@@ -987,8 +987,8 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
             pair_hess_coefs(pa, c.d, ca, cb);
             V3<double> sp;
             if (!pair_dir<R>(iv, c.c, src, pk, rb, limit, sp)) run.bad = 1;
-            const double st = dot(sp, c.t);
-            acc_pHp += ca * st * st + cb * dot(sp, sp);
+            const double st = fdot(sp, c.t);
+            acc_pHp += fma(cb, fdot(sp, sp), ca * st * st);
           }
         }
       }
