@@ -812,8 +812,15 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
   // the step has stopped without an error (so outputs that alias the inputs,
   // which a capacity rerun reads again, stay intact), and a later one
   // supersedes it if the step resumes.
-  const bool early_final = true;
   bool last_is_final = false;
+  // Whether the status in each slot was copied behind an output kernel.  That
+  // of the last chunk may still be on its way when the chunk before it reports
+  // the stop: its status then says nothing about the outputs.
+  bool behind_final[2] = {false, false};
+  auto send_status = [&](int slot) {
+    behind_final[slot] = last_is_final;
+    return enqueue_status(c, slot);
+  };
   // The persistent kernel takes the iterations where it can: one step size,
   // no per-launch timing, and no contact or sparse contact by the segmented
   // scatter (dense contact needs the evenly split pair pass of k_narrow).
@@ -857,7 +864,7 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
       launch_iteration_dir<R>(A, j, c->stream);
       prof_end(c, e);
     }
-    if (early_final && kend == c->iter_max + 1) {
+    if (kend == c->iter_max + 1) {
       const int e = prof_begin(c, PNCG_PROF_PREDICT);
       launch_finalize<R>(A, x_out, v_out, c->stream);
       prof_end(c, e);
@@ -880,12 +887,12 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
   int k = 0, cur = 0;
   StepStatus last_s{};
   int kend = launch_chunk(0, chunk_len(D), 0 /*kModeNormal*/);
-  if ((rc = enqueue_status(c, cur))) return rc;
+  if ((rc = send_status(cur))) return rc;
   while (true) {
     int kn = -1;
     if (ahead && !persist_now && kend <= c->iter_max) {
       kn = launch_chunk(kend, chunk_len(D + rate * (kend - k)), 0);
-      if ((rc = enqueue_status(c, cur ^ 1))) return bail(rc);
+      if ((rc = send_status(cur ^ 1))) return bail(rc);
     }
     if ((rc = wait_status(c, cur))) return bail(rc);
     const StepStatus s = c->h_status[cur];
@@ -908,7 +915,7 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
       D = 0.0;
       k = p;
       kend = launch_chunk(k, chunk_len(D), 2 /*kModeResume*/);
-      if ((rc = enqueue_status(c, cur))) return bail(rc);
+      if ((rc = send_status(cur))) return bail(rc);
       continue;
     }
     if (kend > k) rate = std::max(0.0, (s.D - D) / (kend - k));
@@ -919,7 +926,7 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
       cur ^= 1;
     } else {
       kend = launch_chunk(k, chunk_len(D), persist_now ? kModeContinue : 0);
-      if ((rc = enqueue_status(c, cur))) return bail(rc);
+      if ((rc = send_status(cur))) return bail(rc);
     }
   }
   if (!last_is_final) {
@@ -928,8 +935,8 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
     prof_end(c, ev);
   }
   StepStatus s = last_s;
-  if (sync_end && !last_is_final) {
-    // (behind an output kernel, the status in hand is already the final one)
+  if (sync_end && !behind_final[cur]) {
+    // the outputs, and what the output kernel finds wrong with them
     if ((rc = read_status(c))) return rc;
     s = *c->h_status;
     if ((rc = check_status_err(c, s))) return rc;
