@@ -135,6 +135,7 @@ struct pncg_ctx {
   std::vector<double> vol, Bm;  // Bm: [nT][9] rows of D_m^{-1}
   std::vector<double> E, nu, rho, mass;
   std::vector<uint8_t> vflag;
+  std::vector<uint8_t> lflag;   // vflag | kPairVertex: what the persistent kernel goes by
   std::vector<int> inc, inc_vert;
   int nWaves = 0;
   int model = PNCG_MODEL_NH;   // elastic density (PNCG_MODEL_*)
@@ -177,6 +178,7 @@ struct pncg_ctx {
   int4* d_pv = nullptr;        // [cap] corner vertices of each pair
   // explicit candidate lists (pncg_set_candidates_override), kind in the pair
   bool ovr_set[2] = {false, false};
+  bool ovr_inner = false;       // the point-triangle override names a point that no surface triangle or edge has
   std::vector<int2> ovr[2];
   int2* d_ovr = nullptr;
   long long n_ovr = 0;
@@ -746,6 +748,8 @@ int read_status(pncg_ctx* c) {
 template <typename R>
 bool persist_usable(pncg_ctx* c, const Args<R>& A) {
   if (!c->persist_ok[persist_form(A.model)] || c->profiling || A.split || (A.self && !A.seg)) return false;
+  // (the kernel keeps x and p in memory for the corners of surface triangles and edges only)
+  if (A.self && c->ovr_inner) return false;
   if (c->persist_off > 0) return false;
   signed char& fit = c->persist_fit[A.model][A.self];
   if (fit < 0) {
@@ -1297,9 +1301,6 @@ static int setup_persist(pncg_ctx* c) {
     return PNCG_OK;   // no memory for the tables: the iterations are launched
   }
   if (!T.ok[0] && !T.ok[1]) return PNCG_OK;
-  std::vector<uint8_t> fl(c->vflag);
-  for (int i : c->tris) fl[i] |= kPairVertex;
-  for (int i : c->edges) fl[i] |= kPairVertex;
   PersistArgs& P = T.form[0];
   int rc;
   auto put = [&](auto& vec, auto*& dst) -> int {
@@ -1314,7 +1315,7 @@ static int setup_persist(pncg_ctx* c) {
   if ((rc = put(T.blk, P.blk)) || (rc = put(T.loc_v, P.loc_v)) || (rc = put(T.tet_e, P.tet_e)) ||
       (rc = put(T.tet_l, P.tet_l)) || (rc = put(T.lane, P.lane)) || (rc = put(T.wave_last, P.wave_last)) ||
       (rc = put(T.run, P.run)) || (rc = put(T.seg, P.seg)) || (rc = put(T.chunk, P.chunk)) || (rc = put(T.entry, P.entry)) ||
-      (rc = put(T.dtet, P.dtet)) || (rc = put(T.dvert, P.dvert)) || (rc = put(fl, P.lflag)))
+      (rc = put(T.dtet, P.dtet)) || (rc = put(T.dvert, P.dvert)) || (rc = put(c->lflag, P.lflag)))
     return rc;
   if ((rc = dmalloc(c, &P.slot_grad, 24 * (size_t)P.grid)) || (rc = dmalloc(c, &P.slot_dir, 9 * (size_t)P.grid)) ||
       (rc = dmalloc(c, &P.pgx, 9 * (size_t)c->nV)) || (rc = dmalloc(c, &P.ring, 1)))
@@ -1456,6 +1457,9 @@ int pncg_set_mesh(pncg_ctx* c, int32_t nV, const double* X, int32_t nT, const in
   c->vol = vol;
   c->Bm = Bm;
   c->vflag = fl;
+  for (int i : c->tris) fl[i] |= kPairVertex;
+  for (int i : c->edges) fl[i] |= kPairVertex;
+  c->lflag = fl;
   c->inc = inc;
   c->inc_vert = incv;
   c->nWaves = (int)(inc.size() / kWave);
@@ -1481,7 +1485,7 @@ int pncg_set_mesh(pncg_ctx* c, int32_t nV, const double* X, int32_t nT, const in
   c->d_rp = nullptr;
   c->d_pv = nullptr;
   c->d_ovr = nullptr; c->n_ovr = 0; c->ovr_uploaded = false;
-  c->ovr_set[0] = c->ovr_set[1] = false; c->ovr[0].clear(); c->ovr[1].clear();
+  c->ovr_set[0] = c->ovr_set[1] = c->ovr_inner = false; c->ovr[0].clear(); c->ovr[1].clear();
   c->adj_ready = false; c->d_cgs = nullptr; c->cgs_cap = 0; c->E_uploaded = false;
   c->adj_lam_valid = false;
   c->d_excl_pt = c->d_excl_ee = nullptr; c->n_excl_pt = c->n_excl_ee = 0;
@@ -1731,7 +1735,7 @@ int pncg_set_candidates_override(pncg_ctx* c, int32_t kind, int64_t n, const int
   if (c->state < 1) return fail(c, PNCG_E_STATE, "set_mesh must come first");
   c->list_valid = false;
   if (n < 0) {
-    c->ovr_set[0] = c->ovr_set[1] = false;
+    c->ovr_set[0] = c->ovr_set[1] = c->ovr_inner = false;
     c->ovr[0].clear();
     c->ovr[1].clear();
     c->ovr_uploaded = false;
@@ -1741,6 +1745,7 @@ int pncg_set_candidates_override(pncg_ctx* c, int32_t kind, int64_t n, const int
   if (n > 0 && !pairs) return fail(c, PNCG_E_INVAL, "NULL pairs");
   if (n > (int64_t)INT_MAX / 8) return fail(c, PNCG_E_INVAL, "too many pairs");
   std::vector<int2> lst((size_t)n);
+  bool inner = false;
   for (int64_t i = 0; i < n; ++i) {
     int a = pairs[2 * i], b = pairs[2 * i + 1];
     if (kind == PNCG_KIND_PT) {
@@ -1749,6 +1754,7 @@ int pncg_set_candidates_override(pncg_ctx* c, int32_t kind, int64_t n, const int
       const int* t = c->tris.data() + 3 * (size_t)b;
       if (a == t[0] || a == t[1] || a == t[2])
         return fail(c, PNCG_E_INVAL, "point-triangle pair " + std::to_string(i) + " shares a vertex");
+      inner = inner || !(c->lflag[a] & kPairVertex);
     } else {
       if (a < 0 || a >= c->nE || b < 0 || b >= c->nE || a == b)
         return fail(c, PNCG_E_INVAL, "edge-edge pair " + std::to_string(i) + " out of range or repeated edge");
@@ -1766,6 +1772,7 @@ int pncg_set_candidates_override(pncg_ctx* c, int32_t kind, int64_t n, const int
     if (srt[i].x == srt[i - 1].x && srt[i].y == srt[i - 1].y) return fail(c, PNCG_E_INVAL, "repeated pair");
   c->ovr[kind] = lst;
   c->ovr_set[kind] = true;
+  if (kind == PNCG_KIND_PT) c->ovr_inner = inner;
   c->ovr_uploaded = false;
   HIPCHK(c, hipSetDevice(c->device));
   int rc = upload_override(c);
