@@ -269,6 +269,26 @@ int pncg_set_candidates_override(pncg_ctx* ctx, int32_t kind, int64_t n, const i
  * an earlier step (see pncg_step), so the next step builds its own. */
 int pncg_set_tuning(pncg_ctx* ctx, double skin, int32_t chunk);
 
+/* The persistent kernels (the iterations of a step, and of an adjoint's CG,
+ * in one launch): up to one workgroup on every compute unit, with most of its
+ * LDS, which meet through memory in each iteration and so have to be resident
+ * together.  A launch whose workgroups do not fit beside those of this
+ * process's other contexts is not made; the iterations are launched one by one
+ * then.  Where something else holds compute units (other kernels on the
+ * device, another process) the workgroups wait for one another, up to
+ * max_wait_us in a meeting; a launch that waits longer writes no outputs, the
+ * call starts again with the iterations launched one by one, and so do this
+ * context's next 64 steps or adjoints.  Both forms give the same bits (a step
+ * that had rebuilt the list of pairs by then starts again on a list of its
+ * own, whose sums may round differently).
+ *   max_wait_us  0: the default, 20,000; -1: no wait at all, so that every
+ *                launch gives up (a test of that path)
+ * E_INVAL below -1. */
+int pncg_set_persistent(pncg_ctx* ctx, int32_t max_wait_us);
+/* Persistent launches made, and calls that started again after one, since
+ * pncg_set_mesh. */
+int pncg_get_persistent(pncg_ctx* ctx, int64_t* launches, int64_t* timeouts);
+
 /* Mean rest length of the surface edges given to pncg_set_mesh (0 if
  * none), for the larger-dhat strategy of Sec. 5.1: dhat at 30-70 % of it,
  * with PNCG_CONTACT_REST_EXCLUDE dropping the same-object pairs closer than

@@ -42,7 +42,7 @@ EXPORTS = ("pncg_create", "pncg_destroy", "pncg_last_error", "pncg_set_mesh", "p
            "pncg_batch_set_block", "pncg_batch_step", "pncg_batch_run", "pncg_batch_stats",
            "pncg_batch_autotune", "pncg_batch_set_staging", "pncg_batch_get_config",
            "pncg_batch_set_split", "pncg_set_model", "pncg_batch_set_model", "pncg_run_dev",
-           "pncg_set_candidates_override", "pncg_step_dev_noalloc")
+           "pncg_set_candidates_override", "pncg_step_dev_noalloc", "pncg_set_persistent", "pncg_get_persistent")
 PROF_KINDS = ("narrow", "grad", "dir", "rebuild", "predict")
 
 
@@ -92,6 +92,8 @@ def _load():
         "pncg_step_dev_noalloc": (I32, [P, P, P, D, P, P, C.POINTER(pncg_stats)]),
         "pncg_set_model": (I32, [P, I32]),
         "pncg_batch_set_model": (I32, [P, I32]),
+        "pncg_set_persistent": (I32, [P, I32]),
+        "pncg_get_persistent": (I32, [P, C.POINTER(I64), C.POINTER(I64)]),
         "pncg_mean_boundary_edge": (I32, [P, P]),
         "pncg_set_adjoint_warm_start": (I32, [P, I32]),
         "pncg_step": (I32, [P, P, P, D, P, P, C.POINTER(pncg_stats)]),
@@ -217,6 +219,15 @@ class Context:
 
     def pncg_set_adjoint_warm_start(self, on):
         self._check(_L.pncg_set_adjoint_warm_start(self._h, 1 if on else 0))
+
+    def pncg_set_persistent(self, max_wait_us=0):
+        self._check(_L.pncg_set_persistent(self._h, int(max_wait_us)))
+
+    def pncg_get_persistent(self):
+        """(persistent launches, calls that started again after one) since the mesh was set."""
+        n, t = C.c_int64(), C.c_int64()
+        self._check(_L.pncg_get_persistent(self._h, C.byref(n), C.byref(t)))
+        return n.value, t.value
 
     def pncg_mean_boundary_edge(self):
         out = C.c_double()

@@ -96,9 +96,8 @@ struct UnitsHeld {
   }
 };
 
-#ifndef PNCG_PERSIST_WAIT
-#define PNCG_PERSIST_WAIT 2000000   // longest wait of a meeting, in ticks of the 100 MHz clock (20 ms)
-#endif
+constexpr int kPersistWaitUs = 20000;       // longest wait of a meeting
+constexpr long long kTicksPerUs = 100;      // of the clock that the kernels watch
 
 struct DevBuf {
   void* p = nullptr;
@@ -218,6 +217,8 @@ struct pncg_ctx {
   // persistent iteration kernel: tables and exchange buffers (set_mesh)
   bool persist_ok[2] = {false, false};   // the mesh has tables (by element form, see PersistTables)
   int persist_off = 0;          // after a timed-out meeting: steps that still use the per-iteration launches
+  long long persist_wait = kPersistWaitUs * kTicksPerUs;   // PersistArgs::limit
+  long long persist_launches = 0, persist_timeouts = 0;    // since pncg_set_mesh
   signed char persist_fit[3][2] = {{-1, -1}, {-1, -1}, {-1, -1}};   // by [model][self]: kernel fits (-1 not asked yet)
   int units = 0;                // compute units of the device
   PersistArgs persist[2];
@@ -842,6 +843,7 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
                   held.acquire(c->device, c->persist[0].blocks, c->units);
     if (persist_now) {
       launch_persist<R>(A, c->persist[persist_form(A.model)], k0, mode0, c->stream);
+      ++c->persist_launches;
       launch_finalize<R>(A, x_out, v_out, c->stream);   // writes only if the step has stopped
       last_is_final = true;
       return std::min(k0 + kPersistMaxIters, c->iter_max + 1);
@@ -1156,6 +1158,7 @@ bool cg_persist_usable(pncg_ctx* c, const Args<double>& A) {
 void restart_launches(pncg_ctx* c) {
   persist_clear(c->persist[0], c->nV, c->stream);
   c->persist_off = kPersistBackoff;
+  ++c->persist_timeouts;
 }
 
 // All pointers are device pointers.  Ebar is accumulated.
@@ -1201,8 +1204,10 @@ int adjoint_impl(pncg_ctx* c, const double* x1, double h, const double* xbar, co
     int k = 0, chunk = 16;
     while (true) {
       const int kend = std::min(k + (persist ? kPersistMaxIters : chunk), last + 1);
-      if (persist) launch_cg_persist(A, C, c->cg_persist, k, c->stream);
-      else
+      if (persist) {
+        launch_cg_persist(A, C, c->cg_persist, k, c->stream);
+        ++c->persist_launches;
+      } else
         for (int j = k; j < kend; ++j) launch_cg_iteration(A, C, j, fused, c->stream);
       HIPCHK(c, hipMemcpyAsync(c->h_cgst, c->d_cgst, sizeof(CgStatus), hipMemcpyDeviceToHost, c->stream));
       if ((rc = sync(c))) return rc;
@@ -1291,6 +1296,7 @@ static int setup_persist(pncg_ctx* c) {
   c->persist_ok[0] = c->persist_ok[1] = false;
   c->cg_persist_ok = false;
   c->persist_off = 0;
+  c->persist_launches = c->persist_timeouts = 0;
   for (auto& m : c->cg_persist_fit) m = -1;
   for (auto& m : c->persist_fit) m[0] = m[1] = -1;
   PersistTables T;
@@ -1320,7 +1326,7 @@ static int setup_persist(pncg_ctx* c) {
   if ((rc = dmalloc(c, &P.slot_grad, 24 * (size_t)P.grid)) || (rc = dmalloc(c, &P.slot_dir, 9 * (size_t)P.grid)) ||
       (rc = dmalloc(c, &P.pgx, 9 * (size_t)c->nV)) || (rc = dmalloc(c, &P.ring, 1)))
     return rc;
-  P.limit = PNCG_PERSIST_WAIT;
+  P.limit = c->persist_wait;
   persist_clear(P, c->nV, c->stream);
   // both forms share the tables and the buffers
   c->persist[0] = c->persist[1] = P;
@@ -1707,6 +1713,21 @@ int pncg_set_tuning(pncg_ctx* c, double skin, int32_t chunk) {
   c->skin = skin > 0.0 ? skin : default_skin(c->dhat, c->lmean);
   set_cell(c);
   if (chunk > 0) c->chunk = chunk;
+  return PNCG_OK;
+}
+
+int pncg_set_persistent(pncg_ctx* c, int32_t max_wait_us) {
+  if (!c) return PNCG_E_INVAL;
+  if (max_wait_us < -1) return fail(c, PNCG_E_INVAL, "need max_wait_us >= -1");
+  c->persist_wait = max_wait_us < 0 ? -1 : (max_wait_us ? max_wait_us : kPersistWaitUs) * kTicksPerUs;
+  c->persist[0].limit = c->persist[1].limit = c->cg_persist.P.limit = c->persist_wait;
+  return PNCG_OK;
+}
+
+int pncg_get_persistent(pncg_ctx* c, int64_t* launches, int64_t* timeouts) {
+  if (!c || !launches || !timeouts) return PNCG_E_INVAL;
+  *launches = c->persist_launches;
+  *timeouts = c->persist_timeouts;
   return PNCG_OK;
 }
 

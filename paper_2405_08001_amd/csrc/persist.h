@@ -66,7 +66,7 @@ struct PersistArgs {
   unsigned long long* slot_dir;  // [3][3][grid]
   unsigned long long* pgx;       // [3][nV][3]
   int* ring;                     // set of the next launch's first iteration
-  long long limit;               // longest wait, in ticks of the 100 MHz clock
+  long long limit;               // longest wait, in ticks of the 100 MHz clock (see Wait)
   int cap_own;                   // most own vertices of a block
   int chunks;                    // chunks of a block's waves
   int cap_rp, cap_dg;            // pair entries whose run partials, and pairs whose geometry, fit in LDS

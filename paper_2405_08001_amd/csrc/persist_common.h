@@ -31,14 +31,15 @@ __device__ __forceinline__ double as_double(u64 w) { return __longlong_as_double
 __device__ __forceinline__ float lo_float(u64 w) { return __int_as_float((int)(unsigned)w); }
 __device__ __forceinline__ float hi_float(u64 w) { return __int_as_float((int)(unsigned)(w >> 32)); }
 
-// Watches the clock in a polling loop.
+// Watches the clock in a polling loop.  A negative limit: the first look that
+// finds a word missing is the last.
 struct Wait {
   long long t0, limit;
   int n;
   __device__ __forceinline__ Wait(long long l) : t0(0), limit(l), n(0) {}
   // true when the wait has run out
   __device__ __forceinline__ bool over() {
-    if ((++n & 63) != 0) return false;
+    if ((++n & 63) != 0) return limit < 0;
     const long long t = wall_clock64();
     if (t0 == 0) t0 = t;
     return t - t0 > limit;
