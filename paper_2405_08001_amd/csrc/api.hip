@@ -906,7 +906,11 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
     held.release();
     if (A.self) c->last_ncand = s.n_cand;
     if (s.err & kErrCapacity) return bail(kRestart);
-    if (s.err & kErrSync) return bail(kRestartLaunches);
+    if (s.err & kErrSync) {
+      // the step starts again on the list that it started on
+      if (carry && rebuilds == 0) c->list_valid = true;
+      return bail(kRestartLaunches);
+    }
     if ((rc = check_status_err(c, s))) return bail(rc);
     if (s.stopped) break;
     if (s.paused_at >= 0) {

@@ -1,11 +1,13 @@
 """A persistent launch that gives up a wait (the host sets the limit so that
 every launch does): the call starts again with a launch per iteration and has
-that form's bits, from an intact state, in place, without allocation and from
-a warm start; after 64 calls the persistent kernel runs again.  The other side launches per iteration from the first (profiling on)."""
+that form's bits, from an intact state, in place, without allocation, on a
+carried list and from a warm start; after 64 calls the persistent kernel runs
+again.  The other side launches per iteration from the first (profiling on)."""
 import numpy as np
 import pytest
 
 import scenes
+from scenes import configs
 from helpers import make_ctx
 
 pytestmark = pytest.mark.gpu
@@ -71,6 +73,28 @@ def test_run_in_place_and_after_the_back_off(precision):
     a.pncg_set_persistent(AT_ONCE)
     _same(_run(a, x, v, sc.h, 2), _run(b, x, v, sc.h, 2))
     assert a.pncg_get_persistent() == (5, 2)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_step_on_a_carried_list(precision):
+    """The frame that starts again begins on the list of the frame before."""
+    Xa, Ta = scenes.hex_grid(16, 16, 16, 0.01, origin=(0.0, 0.0, 5e-4))
+    Xb, Tb = scenes.hex_grid(2, 2, 2, 0.01, origin=(0.073, 0.068, 0.1605 + 4e-4))
+    X, tets, oid = scenes.merge_meshes([(Xa, Ta), (Xb, Tb)])
+    sc = configs._scene(X, tets, E=2e5, nu=0.4, rho=1000.0, planes=[[0.0, 0.0, 1.0, 0.0]], dhat=1e-3, kappa=0.1,
+                        h=1e-3, object_id=oid, self_contact=True)
+    v0 = np.zeros_like(sc.X)
+    v0[oid == 1, 2] = -0.1
+    a, b = _pair(sc, precision, iter_max=25, eps=0.0, term="delta_e")
+    _same(_run(a, sc.X, v0, sc.h, 1), _run(b, sc.X, v0, sc.h, 1))
+    before = a.pncg_get_persistent()
+    assert before[0] >= 1 and before[1] == 0
+    a.pncg_set_persistent(AT_ONCE)
+    # (the same state again: within the list that the first step left)
+    ra, rb = _run(a, sc.X, v0, sc.h, 3), _run(b, sc.X, v0, sc.h, 3)
+    assert rb[2][0]["rebuilds"] == 0 and rb[2][0]["n_active"] > 0
+    _same(ra, rb)
+    assert a.pncg_get_persistent() == (before[0] + 1, 1)
 
 
 @pytest.mark.parametrize("precision", [0, 1])
