@@ -280,7 +280,9 @@ int pncg_set_tuning(pncg_ctx* ctx, double skin, int32_t chunk);
  * call starts again with the iterations launched one by one, and so do this
  * context's next 64 steps or adjoints.  Both forms give the same bits (a step
  * that had rebuilt the list of pairs by then starts again on a list of its
- * own, whose sums may round differently).
+ * own, whose sums may round differently).  The kernels' tables are built by
+ * the first step or adjoint after pncg_set_mesh that can use them; without
+ * memory for them the iterations are launched one by one.
  *   max_wait_us  0: the default, 20,000; -1: no wait at all, so that every
  *                launch gives up (a test of that path)
  * E_INVAL below -1. */
@@ -333,10 +335,11 @@ int pncg_step_dev(pncg_ctx* ctx, const double* x_dev, const double* v_dev,
  * scratch (its status record, the per-block partial sums of the
  * per-iteration kernels and one scalar record per iteration) lives in a
  * static device array of 1 MiB that the library holds on every device it
- * runs on until the process ends; the per-vertex state, the tables and
- * exchange buffers of the persistent iteration kernel and the candidate
+ * runs on until the process ends; the per-vertex state and the candidate
  * buffers are the context's, sized by pncg_set_mesh, pncg_set_contact and
- * earlier steps.  Every call on one device shares that device's array, so
+ * earlier steps.  The tables and exchange buffers of the persistent kernel are
+ * those that an earlier step or adjoint of the context built; without them the
+ * iterations are launched one by one, with the same bits.  Every call on one device shares that device's array, so
  * calls that overlap on one device (from two host threads, or on two
  * streams) race and must not be made.  Errors, besides pncg_step_dev's:
  * E_INVAL for iter_max above PNCG_NOALLOC_ITER_MAX or a split step

@@ -214,7 +214,8 @@ struct pncg_ctx {
   long long *d_part_cnt = nullptr, *d_part_off = nullptr, *d_totals = nullptr;
   long long work_cap = 0;
   int grid = 1;
-  // persistent iteration kernel: tables and exchange buffers (set_mesh)
+  // persistent kernels: tables and exchange buffers (build_persist)
+  bool persist_built = false;   // built, or found that there can be none
   bool persist_ok[2] = {false, false};   // the mesh has tables (by element form, see PersistTables)
   int persist_off = 0;          // after a timed-out meeting: steps that still use the per-iteration launches
   long long persist_wait = kPersistWaitUs * kTicksPerUs;   // PersistArgs::limit
@@ -745,13 +746,109 @@ int read_status(pncg_ctx* c) {
 }
 
 // ------------------------------------------------------------------ step
-// Whether the step's iterations can run in the persistent kernel.
+// Tables and exchange buffers of the persistent kernels for the mesh, in one
+// device allocation.  Built when a step or an adjoint first can use them, not
+// by pncg_set_mesh: queries, split steps, the atomic scatter and dense contact
+// never do, and building and uploading takes 0.2 ms at 1,300 tets, 0.8 ms at
+// 13,000 and 3.5 ms at 110,000.  Without memory for them, on the host or the
+// device, or where a block's share does not fit in LDS, the iterations are
+// launched one by one.
+void build_persist(pncg_ctx* c) {
+  c->persist_built = true;
+  unsigned char* base = nullptr;
+  try {
+    PersistTables T;
+    persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, c->precision == PNCG_FP64,
+                  c->nF + c->nE > 0, T);
+    if (!T.ok[0] && !T.ok[1]) return;
+    PersistArgs& P = T.form[0];
+    // first the sizes, then the addresses and copies
+    size_t bytes = 0;
+    bool ok = true;
+    auto place = [&](auto*& dst, const void* src, size_t n) {
+      using E = typename std::remove_reference<decltype(*dst)>::type;
+      if (base) dst = reinterpret_cast<E*>(base + bytes);
+      if (base && src && n)
+        ok = ok && hipMemcpyAsync(base + bytes, src, sizeof(E) * n, hipMemcpyHostToDevice, c->stream) == hipSuccess;
+      bytes = (bytes + sizeof(E) * n + 255) / 256 * 256;
+    };
+    auto layout = [&] {
+      bytes = 0;
+      place(P.blk, T.blk.data(), T.blk.size());
+      place(P.loc_v, T.loc_v.data(), T.loc_v.size());
+      place(P.tet_e, T.tet_e.data(), T.tet_e.size());
+      place(P.tet_l, T.tet_l.data(), T.tet_l.size());
+      place(P.lane, T.lane.data(), T.lane.size());
+      place(P.wave_last, T.wave_last.data(), T.wave_last.size());
+      place(P.run, T.run.data(), T.run.size());
+      place(P.seg, T.seg.data(), T.seg.size());
+      place(P.chunk, T.chunk.data(), T.chunk.size());
+      place(P.entry, T.entry.data(), T.entry.size());
+      place(P.dtet, T.dtet.data(), T.dtet.size());
+      place(P.dvert, T.dvert.data(), T.dvert.size());
+      place(P.lflag, c->lflag.data(), c->lflag.size());
+      place(P.slot_grad, nullptr, 24 * (size_t)P.grid);
+      place(P.slot_dir, nullptr, 9 * (size_t)P.grid);
+      place(P.pgx, nullptr, 9 * (size_t)c->nV);
+      place(P.ring, nullptr, 1);
+    };
+    layout();
+    c->allocs.reserve(c->allocs.size() + 1);
+    if (hipMalloc(reinterpret_cast<void**>(&base), bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    c->allocs.push_back(base);
+    layout();
+    P.limit = c->persist_wait;
+    persist_clear(P, c->nV, c->stream);
+    // (the copies read the tables)
+    ok = hipStreamSynchronize(c->stream) == hipSuccess && ok;
+    if (!ok) {
+      dfree(c, base);
+      return;
+    }
+    // both forms share the tables and the buffers
+    c->persist[0] = c->persist[1] = P;
+    c->persist[1].chunks = T.form[1].chunks;
+    c->persist[1].elem_lds = T.form[1].elem_lds;
+    c->persist[1].cap_rp = T.form[1].cap_rp;
+    c->persist[1].cap_dg = T.form[1].cap_dg;
+    c->persist[1].at = T.form[1].at;
+    c->persist[1].lds = T.form[1].lds;
+    c->persist_ok[0] = T.ok[0];
+    c->persist_ok[1] = T.ok[1];
+    c->cg_persist = T.cg;
+    c->cg_persist.P = P;
+    c->cg_persist_ok = T.cg_ok;
+  } catch (const std::bad_alloc&) {
+  }
+}
+
+// Whether the step's iterations may run in the persistent kernel, as far as
+// its settings go.
+template <typename R>
+bool persist_wanted(const pncg_ctx* c, const Args<R>& A) {
+  if (c->profiling || A.split || (A.self && !A.seg) || c->persist_off > 0) return false;
+  // (the kernel keeps x and p in memory for the corners of surface triangles and edges only)
+  return !(A.self && c->ovr_inner);
+}
+
+// Whether they can: the mesh has tables and the kernel fits.
 template <typename R>
 bool persist_usable(pncg_ctx* c, const Args<R>& A) {
-  if (!c->persist_ok[persist_form(A.model)] || c->profiling || A.split || (A.self && !A.seg)) return false;
-  // (the kernel keeps x and p in memory for the corners of surface triangles and edges only)
-  if (A.self && c->ovr_inner) return false;
-  if (c->persist_off > 0) return false;
+  if (!c->persist_built) {
+    if (c->noalloc) return false;
+    if (A.self) {
+      // dense contact keeps to the launches; before a first step's status is
+      // in, the list itself has to be asked
+      if (hipMemcpyAsync(c->h_n, c->d_ncand, sizeof(long long), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+          hipStreamSynchronize(c->stream) != hipSuccess || 4 * c->h_n[0] > (long long)c->nV)
+        return false;
+    }
+    build_persist(c);
+  }
+  if (!c->persist_ok[persist_form(A.model)]) return false;
   signed char& fit = c->persist_fit[A.model][A.self];
   if (fit < 0) {
     bool ok = false;
@@ -829,7 +926,7 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
   // The persistent kernel takes the iterations where it can: one step size,
   // no per-launch timing, and no contact or sparse contact by the segmented
   // scatter (dense contact needs the evenly split pair pass of k_narrow).
-  const bool may_persist = persist_usable<R>(c, A);
+  const bool may_persist = persist_wanted(c, A);
   bool persist_now = false;
   UnitsHeld held;
   auto launch_chunk = [&](int k0, int m, int mode0) {
@@ -840,7 +937,7 @@ int step_impl(pncg_ctx* c, const double* x_dev, const double* v_dev, double h, d
     // (it starts from a complete x_k: at the step's beginning, after a pause
     // or where it left off, not behind a chunk of launches)
     persist_now = may_persist && (k0 == 0 || mode0 != kModeNormal) && (!A.self || fused) &&
-                  held.acquire(c->device, c->persist[0].blocks, c->units);
+                  persist_usable(c, A) && held.acquire(c->device, c->persist[0].blocks, c->units);
     if (persist_now) {
       launch_persist<R>(A, c->persist[persist_form(A.model)], k0, mode0, c->stream);
       ++c->persist_launches;
@@ -1147,7 +1244,9 @@ int ensure_adjoint(pncg_ctx* c, int cg_max) {
 
 // Whether the adjoint's CG iterations can run in their persistent kernel.
 bool cg_persist_usable(pncg_ctx* c, const Args<double>& A) {
-  if (!c->cg_persist_ok || A.model == kModelCorot || c->profiling || c->persist_off > 0) return false;
+  if (A.model == kModelCorot || c->profiling || c->persist_off > 0) return false;
+  if (!c->persist_built) build_persist(c);
+  if (!c->cg_persist_ok) return false;
   signed char& fit = c->cg_persist_fit[A.model];
   if (fit < 0) {
     bool ok = false;
@@ -1294,60 +1393,6 @@ int grid_for(const pncg_ctx* c) {
 
 }  // namespace
 
-// Tables and exchange buffers of the persistent iteration kernel for the mesh
-// just committed (none if a block's share does not fit in LDS).
-static int setup_persist(pncg_ctx* c) {
-  c->persist_ok[0] = c->persist_ok[1] = false;
-  c->cg_persist_ok = false;
-  c->persist_off = 0;
-  c->persist_launches = c->persist_timeouts = 0;
-  for (auto& m : c->cg_persist_fit) m = -1;
-  for (auto& m : c->persist_fit) m[0] = m[1] = -1;
-  PersistTables T;
-  try {
-    persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, c->precision == PNCG_FP64,
-                  c->nF + c->nE > 0, T);
-  } catch (const std::bad_alloc&) {
-    return PNCG_OK;   // no memory for the tables: the iterations are launched
-  }
-  if (!T.ok[0] && !T.ok[1]) return PNCG_OK;
-  PersistArgs& P = T.form[0];
-  int rc;
-  auto put = [&](auto& vec, auto*& dst) -> int {
-    using T_ = typename std::remove_reference<decltype(vec)>::type::value_type;
-    T_* d = nullptr;
-    int r = dmalloc(c, &d, vec.size());
-    if (r) return r;
-    dst = d;
-    HIPCHK(c, hipMemcpyAsync(d, vec.data(), sizeof(T_) * vec.size(), hipMemcpyHostToDevice, c->stream));
-    return PNCG_OK;
-  };
-  if ((rc = put(T.blk, P.blk)) || (rc = put(T.loc_v, P.loc_v)) || (rc = put(T.tet_e, P.tet_e)) ||
-      (rc = put(T.tet_l, P.tet_l)) || (rc = put(T.lane, P.lane)) || (rc = put(T.wave_last, P.wave_last)) ||
-      (rc = put(T.run, P.run)) || (rc = put(T.seg, P.seg)) || (rc = put(T.chunk, P.chunk)) || (rc = put(T.entry, P.entry)) ||
-      (rc = put(T.dtet, P.dtet)) || (rc = put(T.dvert, P.dvert)) || (rc = put(c->lflag, P.lflag)))
-    return rc;
-  if ((rc = dmalloc(c, &P.slot_grad, 24 * (size_t)P.grid)) || (rc = dmalloc(c, &P.slot_dir, 9 * (size_t)P.grid)) ||
-      (rc = dmalloc(c, &P.pgx, 9 * (size_t)c->nV)) || (rc = dmalloc(c, &P.ring, 1)))
-    return rc;
-  P.limit = c->persist_wait;
-  persist_clear(P, c->nV, c->stream);
-  // both forms share the tables and the buffers
-  c->persist[0] = c->persist[1] = P;
-  c->persist[1].chunks = T.form[1].chunks;
-  c->persist[1].elem_lds = T.form[1].elem_lds;
-  c->persist[1].cap_rp = T.form[1].cap_rp;
-  c->persist[1].cap_dg = T.form[1].cap_dg;
-  c->persist[1].at = T.form[1].at;
-  c->persist[1].lds = T.form[1].lds;
-  c->persist_ok[0] = T.ok[0];
-  c->persist_ok[1] = T.ok[1];
-  c->cg_persist = T.cg;
-  c->cg_persist.P = P;
-  c->cg_persist_ok = T.cg_ok;
-  return sync(c);
-}
-
 // =================================================================== C ABI
 // Objects of the split step must be contiguous vertex ranges (non-decreasing
 // ids) whose tets are contiguous too; the reason if not, else NULL.
@@ -1490,6 +1535,11 @@ int pncg_set_mesh(pncg_ctx* c, int32_t nV, const double* X, int32_t nT, const in
   c->list_valid = false;
   for (void* p : c->allocs) (void)hipFree(p);
   c->allocs.clear();
+  c->persist_built = c->persist_ok[0] = c->persist_ok[1] = c->cg_persist_ok = false;
+  c->persist_off = 0;
+  c->persist_launches = c->persist_timeouts = 0;
+  for (auto& m : c->cg_persist_fit) m = -1;
+  for (auto& m : c->persist_fit) m[0] = m[1] = -1;
   c->d_elem = nullptr; c->d_cand = nullptr; c->cand_cap = 0;
   c->d_cent = nullptr; c->d_cent_tmp = nullptr; c->d_ckey_tmp = nullptr;
   c->d_rp = nullptr;
@@ -1533,7 +1583,6 @@ int pncg_set_mesh(pncg_ctx* c, int32_t nV, const double* X, int32_t nT, const in
     HIPCHK(c, hipMemsetAsync(c->d_wrange, 0, sizeof(int2) * wv.size(), c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
   }
-  if ((rc = setup_persist(c))) return rc;
   c->scal_cap = 0;
   c->d_scal = nullptr;
   c->split_ready = false;

@@ -110,7 +110,9 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
     std::vector<int> entry;     // entry of each local tet
   };
   std::vector<Marks> marks;
-  for (int w = 0; w < workers; ++w) marks.push_back(Marks{Numbers(nV), Numbers(nT), std::vector<int>()});
+  marks.reserve(workers);
+  auto add_marks = [&] { marks.push_back(Marks{Numbers(nV), Numbers(nT), std::vector<int>()}); };
+  add_marks();
   for (int p = 0; p < blocks; ++p) {
     PersistBlock& B = T.blk[p];
     int b0, e0, b1, e1;
@@ -240,10 +242,12 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
     int most = 0, at = 0;
     for (int p = 0; p < blocks; ++p) {
       const PersistBlock& B = T.blk[p];
-      int lo = nV, hi = -1;
-      for (size_t i = (size_t)B.w0 * kWave; i < (size_t)(B.w0 + B.nw) * kWave; ++i)
-        if (inc_vert[i] >= 0) lo = std::min(lo, inc_vert[i]), hi = std::max(hi, inc_vert[i]);
-      if (hi - lo + 1 > most) most = hi - lo + 1, at = p;
+      // (its vertices are consecutive: the first lane's to the last one's that has any)
+      size_t i = (size_t)B.w0 * kWave, j = i + (size_t)B.nw * kWave;
+      while (i < j && inc_vert[i] < 0) ++i;
+      while (i < j && inc_vert[j - 1] < 0) --j;
+      const int own = i < j ? inc_vert[j - 1] - inc_vert[i] + 1 : 0;
+      if (own > most) most = own, at = p;
     }
     number(0, at);
     caps(T.blk[at]);
@@ -251,6 +255,7 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
     if (!layout(A, 8, 0, 0) && !layout(A, 0, 0, 0)) return;
     done = at;
   }
+  while ((int)marks.size() < workers) add_marks();
   for_blocks(blocks, workers, [&](int wk, int p) {
     if (p != done) number(wk, p);
   });
