@@ -82,11 +82,11 @@ constexpr int kRec = 12;              // reals of an element record in LDS (11, 
 constexpr int kRunPartials = 256;     // pair entries of a block with run partials in LDS
 constexpr size_t kPairGeom = 88;      // bytes of a PairGeom (persist.hip); one wave of them per logical block
 constexpr uint8_t kPairVertex = 4;    // corner of a surface triangle or edge (beside kFixed, kSurface)
-constexpr size_t kPersistLds = 158 * 1024;   // of the 160 KiB of a compute unit, less the static arrays
+// Dynamic LDS of a block: the 160 KiB of a compute unit less the kernels'
+// static arrays (k_persist's 4,016 bytes at most, k_cg_persist's 2,256).
+constexpr size_t kPersistLds = 160 * 1024 - 4016, kCgLds = 160 * 1024 - 2256;
 constexpr int kPersistMaxIters = 512;  // iterations of one launch (the host looks at the error bits between launches)
 
-// Host-built tables of PersistArgs, and the layouts of the two element forms:
-// [0] by tet, [1] by (tet, corner) lane for the corotated models.
 // The adjoint's persistent CG kernel on the same tables.  Local vertices: x, z,
 // p, w; own ones: q, diag, lam (3 doubles each), m, fl, run; the rest as in
 // PersistLayout, with three values per slot.
@@ -110,6 +110,8 @@ struct PersistTable {
   T* data() { return d.get(); }
   size_t size() const { return n; }
 };
+// Host-built tables of PersistArgs, and the layouts of the two element forms:
+// [0] by tet, [1] by (tet, corner) lane for the corotated models.
 struct PersistTables {
   std::vector<PersistBlock> blk;
   PersistTable<int> loc_v, tet_e;

@@ -310,7 +310,7 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
     put(L.run, 4 * cap_own, 4);
     put(L.fl, cap_own, 1);
     T.cg.lds = o;
-    T.cg_ok = o <= kPersistLds;
+    T.cg_ok = o <= kCgLds;
   }
   Lists<PersistEntry> entry(blocks);
   Lists<ushort2> seg(blocks);
