@@ -18,6 +18,11 @@ struct CgScal {
   double pq;     // p_k . H p_k          (update launch of k)
 };
 
+// r_k . z_k from the sums of iteration k - 1 (k_cg_fused)
+__device__ __forceinline__ double cg_next_rz(double alpha, double rz, double rw, double qz, double qw) {
+  return fma(alpha * alpha, qw, fma(-alpha, rw + qz, rz));
+}
+
 struct CgStatus {
   int stopped;   // CG has ended
   int iters;     // CG iterations made (updates of lambda)

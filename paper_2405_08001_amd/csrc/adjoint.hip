@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(kCgBlock) k_cg_fused(Args<double> A, AdjArgs C
   if (k > 0) {
     if (!(pq > 0.0) || !isfinite(pq)) { stop(2); return; }
     alpha = rz / pq;
-    const double rz_new = rz - alpha * (rw + qz) + alpha * alpha * qw;
+    const double rz_new = cg_next_rz(alpha, rz, rw, qz, qw);
     beta = rz_new > 0.0 ? rz_new / rz : 0.0;
     if (lead) {
       C.scal[k - 1].alpha = alpha;
@@ -238,10 +238,10 @@ __global__ void __launch_bounds__(kCgBlock) k_cg_fused(Args<double> A, AdjArgs C
         const double* pl = A.planes.p[j];
         const double d = plane_dist(pl, x);
         if (d > 0.0 && d < A.dhat) {
-          const double c = A.kappa * barrier_d2b(d, A.dhat) * (pl[0] * p.x + pl[1] * p.y + pl[2] * p.z);
-          hv[0] += c * pl[0];
-          hv[1] += c * pl[1];
-          hv[2] += c * pl[2];
+          const double c = plane_Hp(A.kappa, pl, d, A.dhat, p);
+          hv[0] = fma(c, pl[0], hv[0]);
+          hv[1] = fma(c, pl[1], hv[1]);
+          hv[2] = fma(c, pl[2], hv[2]);
         }
       }
     }
@@ -357,10 +357,10 @@ __global__ void __launch_bounds__(kSBlock) k_cg_hv(Args<double> A, AdjArgs C, in
         const double* pl = A.planes.p[j];
         const double d = plane_dist(pl, x);
         if (d > 0.0 && d < A.dhat) {
-          const double c = A.kappa * barrier_d2b(d, A.dhat) * (pl[0] * p.x + pl[1] * p.y + pl[2] * p.z);
-          hv[0] += c * pl[0];
-          hv[1] += c * pl[1];
-          hv[2] += c * pl[2];
+          const double c = plane_Hp(A.kappa, pl, d, A.dhat, p);
+          hv[0] = fma(c, pl[0], hv[0]);
+          hv[1] = fma(c, pl[1], hv[1]);
+          hv[2] = fma(c, pl[2], hv[2]);
         }
       }
     }

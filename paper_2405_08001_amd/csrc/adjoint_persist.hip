@@ -168,8 +168,9 @@ __global__ void __launch_bounds__(kCgThreads) k_cg_persist(CgArgs) {
     const ArgPtr<CgArgs> K = kernel_args<CgArgs>();
     const double* Pv = LDS_AT(double, p);
     double* res = LDS_AT(double, res);
-    const HpTet<double> hp =
-        i23_Hp_tet(T.kin, T.B, T.psi33, at3(Pv, v.x), at3(Pv, v.y), at3(Pv, v.z), at3(Pv, v.w));
+    V3<double> d[3];
+    dF_cols(T.B, at3(Pv, v.x), at3(Pv, v.y), at3(Pv, v.z), at3(Pv, v.w), d);
+    const HpTet<double> hp = i23_Hp_tet(T.kin, T.psi33, d);
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const unsigned short to = en.slot[a];
@@ -221,7 +222,7 @@ __global__ void __launch_bounds__(kCgThreads) k_cg_persist(CgArgs) {
           reason = 2;
         } else {
           alpha = rz / pq;
-          const double rz_new = fma(alpha * alpha, qw, fma(-alpha, rw + qz, rz));
+          const double rz_new = cg_next_rz(alpha, rz, rw, qz, qw);
           beta = rz_new > 0.0 ? rz_new / rz : 0.0;
         }
       }
@@ -306,7 +307,7 @@ __global__ void __launch_bounds__(kCgThreads) k_cg_persist(CgArgs) {
             const double* pl = planes + 4 * a;
             const double d = plane_dist(pl, x), dhat = K->A.dhat;
             if (d > 0.0 && d < dhat)
-              q = fma(K->A.kappa * barrier_d2b(d, dhat) * fma(pl[2], p.z, fma(pl[0], p.x, pl[1] * p.y)), pl[j], q);
+              q = fma(plane_Hp(K->A.kappa, pl, d, dhat, p), pl[j], q);
           }
         }
         if (fl & kFixed) q = 0.0;
@@ -333,12 +334,12 @@ __global__ void __launch_bounds__(kCgThreads) k_cg_persist(CgArgs) {
             const int l = (int)m.y + __popcll(m.x & ((1ull << lane) - 1));
             const V3<double> p = at3(Pv, l), q = at3(Q, l), z = at3(Z, l), d = at3(D, l), wq = at3(W, l);
             const V3<double> r = mk3(d.x * z.x, d.y * z.y, d.z * z.z);
-            acc[0] += fdot(p, q);
-            acc[1] += fdot(r, z);
-            acc[2] += fdot(r, r);
-            acc[3] += fdot(r, wq);
-            acc[4] += fdot(q, z);
-            acc[5] += fdot(q, wq);
+            acc[0] += dot(p, q);
+            acc[1] += dot(r, z);
+            acc[2] += dot(r, r);
+            acc[3] += dot(r, wq);
+            acc[4] += dot(q, z);
+            acc[5] += dot(q, wq);
           }
         }
         const double r = row_sums6(acc);

@@ -5,6 +5,13 @@
 //
 // Real is the element/vector type (float in the mixed form, double in the
 // plain form).  Distances, barrier terms and positions are always double.
+//
+// Fused operations are written out.  A launch per iteration and the persistent
+// kernels evaluate the same terms, and which of them runs may depend on what
+// else uses the device, so they have to round alike; left to the compiler, which
+// product of a b + c d it fuses depends on the kernel around it.  YX: the
+// products of the first two components trade places (the order that results
+// have had in the places where it is used).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,11 +33,30 @@ template <typename T>
 __host__ __device__ __forceinline__ V3<T> operator-(V3<T> a, V3<T> b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
 template <typename T>
 __host__ __device__ __forceinline__ V3<T> operator*(T s, V3<T> a) { return {s * a.x, s * a.y, s * a.z}; }
+template <bool YX = false, typename T>
+__host__ __device__ __forceinline__ T dot(V3<T> a, V3<T> b) {
+  return std::fma(a.z, b.z, YX ? std::fma(a.y, b.y, a.x * b.x) : std::fma(a.x, b.x, a.y * b.y));
+}
+// a b - c d
 template <typename T>
-__host__ __device__ __forceinline__ T dot(V3<T> a, V3<T> b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
+__host__ __device__ __forceinline__ T mdiff(T a, T b, T c, T d) { return std::fma(a, b, -(c * d)); }
 template <typename T>
 __host__ __device__ __forceinline__ V3<T> cross(V3<T> a, V3<T> b) {
-  return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
+  return {mdiff(a.y, b.z, a.z, b.y), mdiff(a.z, b.x, a.x, b.z), mdiff(a.x, b.y, a.y, b.x)};
+}
+// s a + b, component by component
+template <typename T>
+__host__ __device__ __forceinline__ V3<T> fma3(T s, V3<T> a, V3<T> b) {
+  return {std::fma(s, a.x, b.x), std::fma(s, a.y, b.y), std::fma(s, a.z, b.z)};
+}
+// b0 a0 + b1 a1 + b2 a2
+template <bool YX = false, typename T>
+__host__ __device__ __forceinline__ V3<T> lin3(T b0, T b1, T b2, V3<T> a0, V3<T> a1, V3<T> a2) {
+  return fma3(b2, a2, YX ? fma3(b1, a1, b0 * a0) : fma3(b0, a0, b1 * a1));
+}
+template <typename T>
+__host__ __device__ __forceinline__ V3<T> lin3(V3<T> b, const V3<T> (&a)[3]) {
+  return lin3(b.x, b.y, b.z, a[0], a[1], a[2]);
 }
 template <typename T, typename U>
 __host__ __device__ __forceinline__ V3<T> cast3(V3<U> a) { return {T(a.x), T(a.y), T(a.z)}; }
@@ -46,13 +72,13 @@ __device__ __forceinline__ double barrier_b(double d, double dhat) {
 __device__ __forceinline__ double barrier_db(double d, double dhat) {
   if (d >= dhat) return 0.0;
   double e = d - dhat;
-  return -2.0 * e * log(d / dhat) - e * e / d;
+  return fma(-2.0 * e, log(d / dhat), -(e * e / d));
 }
 __device__ __forceinline__ double barrier_d2b(double d, double dhat) {
   if (d >= dhat) return 0.0;
   double e = d - dhat;
   double q = e / d;
-  return -2.0 * log(d / dhat) - 4.0 * q + q * q;
+  return fma(q, q, fma(-2.0, log(d / dhat), -(4.0 * q)));
 }
 
 // ------------------------------------------------------- closest points
@@ -63,51 +89,35 @@ struct Closest {
   double d;
 };
 
-// a.b and a b - c d of the closest points.  FUSED: with the fused operations
-// written out, as the compiler chooses them in the per-iteration launches (in
-// a kernel of another shape it may take the products in the other order, one
-// unit in the last place away).
-template <bool FUSED>
-__device__ __forceinline__ double cdot(V3<double> a, V3<double> b) {
-  if constexpr (FUSED) return fma(a.z, b.z, fma(a.x, b.x, a.y * b.y));
-  else return dot(a, b);
-}
-template <bool FUSED>
-__device__ __forceinline__ double mdiff(double a, double b, double c, double d) {
-  if constexpr (FUSED) return fma(a, b, -(c * d));
-  else return a * b - c * d;
-}
-
 // Point x0 against triangle (x1, x2, x3): barycentric region tests on the
 // dot products of the edge vectors with the point offsets (the Voronoi
 // region method of Ericson, Real-Time Collision Detection, 2005, Sec. 5.1.5).
-template <bool FUSED = false>
 __device__ __forceinline__ Closest closest_pt(V3<double> x0, V3<double> x1, V3<double> x2, V3<double> x3) {
   V3<double> ab = x2 - x1, ac = x3 - x1, ap = x0 - x1;
-  double d1 = cdot<FUSED>(ab, ap), d2 = cdot<FUSED>(ac, ap);
+  double d1 = dot(ab, ap), d2 = dot(ac, ap);
   double v, w;  // weights of x2 and x3; x1 gets 1 - v - w
   if (d1 <= 0.0 && d2 <= 0.0) {
     v = 0.0; w = 0.0;
   } else {
     V3<double> bp = x0 - x2;
-    double d3 = cdot<FUSED>(ab, bp), d4 = cdot<FUSED>(ac, bp);
+    double d3 = dot(ab, bp), d4 = dot(ac, bp);
     if (d3 >= 0.0 && d4 <= d3) {
       v = 1.0; w = 0.0;
     } else {
-      double vc = mdiff<FUSED>(d1, d4, d3, d2);
+      double vc = mdiff(d1, d4, d3, d2);
       if (vc <= 0.0 && d1 >= 0.0 && d3 <= 0.0) {
         v = d1 / (d1 - d3); w = 0.0;
       } else {
         V3<double> cp = x0 - x3;
-        double d5 = cdot<FUSED>(ab, cp), d6 = cdot<FUSED>(ac, cp);
+        double d5 = dot(ab, cp), d6 = dot(ac, cp);
         if (d6 >= 0.0 && d5 <= d6) {
           v = 0.0; w = 1.0;
         } else {
-          double vb = mdiff<FUSED>(d5, d2, d1, d6);
+          double vb = mdiff(d5, d2, d1, d6);
           if (vb <= 0.0 && d2 >= 0.0 && d6 <= 0.0) {
             v = 0.0; w = d2 / (d2 - d6);
           } else {
-            double va = mdiff<FUSED>(d3, d6, d5, d4);
+            double va = mdiff(d3, d6, d5, d4);
             if (va <= 0.0 && (d4 - d3) >= 0.0 && (d5 - d6) >= 0.0) {
               w = (d4 - d3) / ((d4 - d3) + (d5 - d6));
               v = 1.0 - w;
@@ -126,9 +136,8 @@ __device__ __forceinline__ Closest closest_pt(V3<double> x0, V3<double> x1, V3<d
   r.c[1] = -(1.0 - v - w);
   r.c[2] = -v;
   r.c[3] = -w;
-  r.t = ap - v * ab;
-  r.t = r.t - w * ac;
-  r.d = sqrt(cdot<FUSED>(r.t, r.t));
+  r.t = fma3(-w, ac, fma3(-v, ab, ap));
+  r.d = sqrt(dot(r.t, r.t));
   return r;
 }
 
@@ -137,15 +146,14 @@ __device__ __forceinline__ Closest closest_pt(V3<double> x0, V3<double> x1, V3<d
 // clamped; u from s; if u leaves [0,1] it is clamped and s recomputed.
 // Parallel edges ((d1.d1)(d2.d2) - (d1.d2)^2 <= 1e-12 (d1.d1)(d2.d2)) start
 // from s = 0.
-template <bool FUSED = false>
 __device__ __forceinline__ Closest closest_ee(V3<double> x0, V3<double> x1, V3<double> x2, V3<double> x3) {
   V3<double> d1 = x1 - x0, d2 = x3 - x2, r = x0 - x2;
-  double a = cdot<FUSED>(d1, d1), e = cdot<FUSED>(d2, d2), f = cdot<FUSED>(d2, r);
-  double c = cdot<FUSED>(d1, r), b = cdot<FUSED>(d1, d2);
-  double den = mdiff<FUSED>(a, e, b, b);
+  double a = dot(d1, d1), e = dot(d2, d2), f = dot(d2, r);
+  double c = dot(d1, r), b = dot(d1, d2);
+  double den = mdiff(a, e, b, b);
   double s = 0.0, u;
-  if (den > 1e-12 * a * e) s = fmin(fmax(mdiff<FUSED>(b, f, c, e) / den, 0.0), 1.0);
-  u = (b * s + f) / e;
+  if (den > 1e-12 * a * e) s = fmin(fmax(mdiff(b, f, c, e) / den, 0.0), 1.0);
+  u = fma(b, s, f) / e;
   if (u < 0.0) {
     u = 0.0;
     s = fmin(fmax(-c / a, 0.0), 1.0);
@@ -158,9 +166,8 @@ __device__ __forceinline__ Closest closest_ee(V3<double> x0, V3<double> x1, V3<d
   out.c[1] = s;
   out.c[2] = -(1.0 - u);
   out.c[3] = -u;
-  out.t = r + s * d1;
-  out.t = out.t - u * d2;
-  out.d = sqrt(cdot<FUSED>(out.t, out.t));
+  out.t = fma3(-u, d2, fma3(s, d1, r));
+  out.d = sqrt(dot(out.t, out.t));
   return out;
 }
 
@@ -188,7 +195,7 @@ __device__ __forceinline__ Kin<R> kinematics(const R* B, V3<double> x0, V3<doubl
   V3<R> e1 = cast3<R>(x1 - x0), e2 = cast3<R>(x2 - x0), e3 = cast3<R>(x3 - x0);
   Kin<R> k;
 #pragma unroll
-  for (int j = 0; j < 3; ++j) k.f[j] = B[j] * e1 + B[3 + j] * e2 + B[6 + j] * e3;
+  for (int j = 0; j < 3; ++j) k.f[j] = lin3(B[j], B[3 + j], B[6 + j], e1, e2, e3);
   k.c[0] = cross(k.f[1], k.f[2]);
   k.c[1] = cross(k.f[2], k.f[0]);
   k.c[2] = cross(k.f[0], k.f[1]);
@@ -208,30 +215,14 @@ __device__ __forceinline__ V3<R> shape_vec(const R* B, int a) {
   return a < 2 ? lo : hi;
 }
 
-// dot and cross with the fused operations spelled out
-template <typename R>
-__device__ __forceinline__ R fdot(V3<R> a, V3<R> b) { return std::fma(a.z, b.z, std::fma(a.x, b.x, a.y * b.y)); }
-template <typename R>
-__device__ __forceinline__ V3<R> fcross(V3<R> a, V3<R> b) {
-  return mk3(std::fma(a.y, b.z, -(a.z * b.y)), std::fma(a.z, b.x, -(a.x * b.z)), std::fma(a.x, b.y, -(a.y * b.x)));
-}
-
-// sum_j b_j col_j
-template <typename R>
-__device__ __forceinline__ V3<R> lin3(V3<R> b, const V3<R> (&col)[3]) {
-  return mk3(std::fma(b.z, col[2].x, std::fma(b.x, col[0].x, b.y * col[1].x)),
-             std::fma(b.z, col[2].y, std::fma(b.x, col[0].y, b.y * col[1].y)),
-             std::fma(b.z, col[2].z, std::fma(b.x, col[0].z, b.y * col[1].z)));
-}
-
 // Psi_3 and Psi_33 of the Neo-Hookean density times V_e:
 //   V Psi_3  = (V lam log J - V mu) / J
 //   V Psi_33 = (V mu + V lam (1 - log J)) / J^2
 template <typename R>
 __device__ __forceinline__ void nh_coeffs(const Kin<R>& k, R vmu, R vlam, R& vpsi3, R& vpsi33) {
   R iJ = R(1) / k.J;
-  vpsi3 = (vlam * k.lnJ - vmu) * iJ;
-  vpsi33 = (vmu + vlam * (R(1) - k.lnJ)) * iJ * iJ;
+  vpsi3 = std::fma(vlam, k.lnJ, -vmu) * iJ;
+  vpsi33 = std::fma(vlam, R(1) - k.lnJ, vmu) * iJ * iJ;
 }
 
 // The I2 and I3 parts of a density with constant Psi_2 and a function of
@@ -243,10 +234,9 @@ __device__ __forceinline__ void nh_coeffs(const Kin<R>& k, R vmu, R vlam, R& vps
 template <typename R>
 __device__ __forceinline__ void i23_grad_diag(const Kin<R>& k, R a2, R vpsi3, R vpsi33, V3<R> ba, V3<R>& g,
                                               V3<R>& dg) {
-  // (the fused operations spelled out, so that every kernel rounds them alike)
   const V3<R> Fb = lin3(ba, k.f), Cb = lin3(ba, k.c);
-  g = mk3(std::fma(a2, Fb.x, vpsi3 * Cb.x), std::fma(a2, Fb.y, vpsi3 * Cb.y), std::fma(a2, Fb.z, vpsi3 * Cb.z));
-  const R bb = a2 * std::fma(ba.z, ba.z, std::fma(ba.x, ba.x, ba.y * ba.y));
+  g = fma3(a2, Fb, vpsi3 * Cb);
+  const R bb = a2 * dot(ba, ba);
   dg = mk3(std::fma(vpsi33 * Cb.x, Cb.x, bb), std::fma(vpsi33 * Cb.y, Cb.y, bb), std::fma(vpsi33 * Cb.z, Cb.z, bb));
 }
 
@@ -255,62 +245,47 @@ template <typename R>
 __device__ __forceinline__ void dF_cols(const R* B, V3<R> p0, V3<R> p1, V3<R> p2, V3<R> p3, V3<R> d[3]) {
   V3<R> q1 = p1 - p0, q2 = p2 - p0, q3 = p3 - p0;
 #pragma unroll
-  for (int j = 0; j < 3; ++j) d[j] = B[j] * q1 + B[3 + j] * q2 + B[6 + j] * q3;
+  for (int j = 0; j < 3; ++j) d[j] = lin3(B[j], B[3 + j], B[6 + j], q1, q2, q3);
 }
 
 // p^T (d2 Psi/dx2) p / (without h^2), I2 and I3 parts:
 //   V [2 Psi_2 |dF|^2 + Psi_33 (cof F : dF)^2
 //      + 2 Psi_3 (f0.(d1 x d2) + f1.(d2 x d0) + f2.(d0 x d1))]
-template <typename R>
+template <bool YX = false, typename R>
 __device__ __forceinline__ R i23_pHp(const Kin<R>& k, R a2, R vpsi3, R vpsi33, const V3<R> d[3]) {
-  R dd = dot(d[0], d[0]) + dot(d[1], d[1]) + dot(d[2], d[2]);
-  R cd = dot(k.c[0], d[0]) + dot(k.c[1], d[1]) + dot(k.c[2], d[2]);
+  R dd = dot<YX>(d[0], d[0]) + dot<YX>(d[1], d[1]) + dot<YX>(d[2], d[2]);
+  R cd = dot<YX>(k.c[0], d[0]) + dot<YX>(k.c[1], d[1]) + dot<YX>(k.c[2], d[2]);
   R mix = dot(k.f[0], cross(d[1], d[2])) + dot(k.f[1], cross(d[2], d[0])) + dot(k.f[2], cross(d[0], d[1]));
-  return a2 * dd + vpsi33 * cd * cd + R(2) * vpsi3 * mix;
+  return std::fma(R(2) * vpsi3, mix, std::fma(a2, dd, vpsi33 * cd * cd));
 }
 
 // (H p)_a / h^2, I2 and I3 parts: V dP b_a with
 //   dP = 2 Psi_2 dF + Psi_33 (cof F : dF) cof F + Psi_3 dcof,
 //   dcof = [d1 x f2 + f1 x d2, d2 x f0 + f2 x d0, d0 x f1 + f0 x d1]
-template <typename R>
-__device__ __forceinline__ V3<R> i23_Hp(const Kin<R>& k, R a2, R vpsi3, R vpsi33, const V3<R> d[3], V3<R> ba) {
-  R cd = dot(k.c[0], d[0]) + dot(k.c[1], d[1]) + dot(k.c[2], d[2]);
-  V3<R> dc0 = cross(d[1], k.f[2]) + cross(k.f[1], d[2]);
-  V3<R> dc1 = cross(d[2], k.f[0]) + cross(k.f[2], d[0]);
-  V3<R> dc2 = cross(d[0], k.f[1]) + cross(k.f[0], d[1]);
-  V3<R> db = ba.x * d[0] + ba.y * d[1] + ba.z * d[2];
-  V3<R> cb = ba.x * k.c[0] + ba.y * k.c[1] + ba.z * k.c[2];
-  V3<R> dcb = ba.x * dc0 + ba.y * dc1 + ba.z * dc2;
-  return a2 * db + (vpsi33 * cd) * cb + vpsi3 * dcb;
-}
-
-// The same in two parts, what the corners of a tet share and a corner's, with
-// the fused operations spelled out as the compiler chooses them for i23_Hp in
-// the adjoint's CG iteration.
+// In two parts, what the corners of a tet share and a corner's.
 template <typename R>
 struct HpTet {
   R s;          // Psi_33 (cof F : dF)
   V3<R> d[3], dc[3];   // dF, dcof
 };
-template <typename R>
-__device__ __forceinline__ HpTet<R> i23_Hp_tet(const Kin<R>& k, const R* B, R vpsi33, V3<R> p0, V3<R> p1, V3<R> p2,
-                                               V3<R> p3) {
+template <bool YX = false, typename R>
+__device__ __forceinline__ HpTet<R> i23_Hp_tet(const Kin<R>& k, R vpsi33, const V3<R> d[3]) {
   HpTet<R> h;
-  const V3<R> q[3] = {p1 - p0, p2 - p0, p3 - p0};
 #pragma unroll
-  for (int j = 0; j < 3; ++j) h.d[j] = lin3(mk3(B[j], B[3 + j], B[6 + j]), q);
-  const V3<R>(&d)[3] = h.d;
-  h.s = vpsi33 * (fdot(k.c[2], d[2]) + (fdot(k.c[0], d[0]) + fdot(k.c[1], d[1])));
-  h.dc[0] = fcross(d[1], k.f[2]) + fcross(k.f[1], d[2]);
-  h.dc[1] = fcross(d[2], k.f[0]) + fcross(k.f[2], d[0]);
-  h.dc[2] = fcross(d[0], k.f[1]) + fcross(k.f[0], d[1]);
+  for (int j = 0; j < 3; ++j) h.d[j] = d[j];
+  h.s = vpsi33 * (dot<YX>(k.c[0], d[0]) + dot<YX>(k.c[1], d[1]) + dot<YX>(k.c[2], d[2]));
+  h.dc[0] = cross(d[1], k.f[2]) + cross(k.f[1], d[2]);
+  h.dc[1] = cross(d[2], k.f[0]) + cross(k.f[2], d[0]);
+  h.dc[2] = cross(d[0], k.f[1]) + cross(k.f[0], d[1]);
   return h;
 }
 template <typename R>
 __device__ __forceinline__ V3<R> i23_Hp_corner(const Kin<R>& k, const HpTet<R>& h, R a2, R vpsi3, V3<R> ba) {
-  const V3<R> db = lin3(ba, h.d), cb = lin3(ba, k.c), dcb = lin3(ba, h.dc);
-  return mk3(std::fma(vpsi3, dcb.x, std::fma(a2, db.x, h.s * cb.x)), std::fma(vpsi3, dcb.y, std::fma(a2, db.y, h.s * cb.y)),
-             std::fma(vpsi3, dcb.z, std::fma(a2, db.z, h.s * cb.z)));
+  return fma3(vpsi3, lin3(ba, h.dc), fma3(a2, lin3(ba, h.d), h.s * lin3(ba, k.c)));
+}
+template <bool YX = false, typename R>
+__device__ __forceinline__ V3<R> i23_Hp(const Kin<R>& k, R a2, R vpsi3, R vpsi33, const V3<R> d[3], V3<R> ba) {
+  return i23_Hp_corner(k, i23_Hp_tet<YX>(k, vpsi33, d), a2, vpsi3, ba);
 }
 
 // Neo-Hookean (Sec. 3.1): 2 Psi_2 = mu.
@@ -330,7 +305,7 @@ template <typename R>
 __device__ __forceinline__ V3<R> nh_Hp(const Kin<R>& k, R vmu, R vlam, const V3<R> d[3], V3<R> ba) {
   R vpsi3, vpsi33;
   nh_coeffs(k, vmu, vlam, vpsi3, vpsi33);
-  return i23_Hp(k, vmu, vpsi3, vpsi33, d, ba);
+  return i23_Hp<true>(k, vmu, vpsi3, vpsi33, d, ba);
 }
 
 // V Psi(F) = V mu/2 (I2 - 3) - V mu log J + V lam/2 (log J)^2
@@ -403,15 +378,15 @@ __device__ __forceinline__ void jacobi_rot(R& app, R& aqq, R& apq, R& arp, R& ar
   const R t = std::copysign(pol_rcp(std::fabs(th) + pol_sqrt(std::fma(th, th, R(1)))), th);
   const R c = pol_rsq(std::fma(t, t, R(1)));
   const R sn = t * c;
-  app -= t * apq;
-  aqq += t * apq;
+  app = std::fma(-t, apq, app);
+  aqq = std::fma(t, apq, aqq);
   apq = R(0);
   const R rp = arp, rq = arq;
-  arp = c * rp - sn * rq;
-  arq = sn * rp + c * rq;
+  arp = mdiff(c, rp, sn, rq);
+  arq = std::fma(c, rq, sn * rp);
   const V3<R> p = vp, q = vq;
-  vp = mk3(c * p.x - sn * q.x, c * p.y - sn * q.y, c * p.z - sn * q.z);
-  vq = mk3(sn * p.x + c * q.x, sn * p.y + c * q.y, sn * p.z + c * q.z);
+  vp = mk3(mdiff(c, p.x, sn, q.x), mdiff(c, p.y, sn, q.y), mdiff(c, p.z, sn, q.z));
+  vq = fma3(c, q, sn * p);
 }
 
 // Jacobi sweeps: enough for rounding-level off-diagonals from any start.
@@ -445,11 +420,11 @@ __device__ __forceinline__ bool polar_rv(const V3<R> f[3], Polar<R>& P) {
   if (a00 < a22) { R t = a00; a00 = a22; a22 = t; V3<R> w = v0; v0 = v2; v2 = w; }
   if (a11 < a22) { R t = a11; a11 = a22; a22 = t; V3<R> w = v1; v1 = v2; v2 = w; }
   v2 = cross(v0, v1);
-  const V3<R> Fv0 = v0.x * f[0] + v0.y * f[1] + v0.z * f[2];
-  const V3<R> Fv1 = v1.x * f[0] + v1.y * f[1] + v1.z * f[2];
-  const V3<R> Fv2 = v2.x * f[0] + v2.y * f[1] + v2.z * f[2];
+  const V3<R> Fv0 = lin3(v0.x, v0.y, v0.z, f[0], f[1], f[2]);
+  const V3<R> Fv1 = lin3<true>(v1.x, v1.y, v1.z, f[0], f[1], f[2]);
+  const V3<R> Fv2 = lin3(v2.x, v2.y, v2.z, f[0], f[1], f[2]);
   const V3<R> u0 = pol_rsq(dot(Fv0, Fv0)) * Fv0;
-  const V3<R> w1 = Fv1 - dot(u0, Fv1) * u0;
+  const V3<R> w1 = fma3(-dot(u0, Fv1), u0, Fv1);
   const V3<R> u1 = pol_rsq(dot(w1, w1)) * w1;
   const V3<R> u2 = cross(u0, u1);
   P.u[0] = u0; P.u[1] = u1; P.u[2] = u2;
@@ -467,19 +442,28 @@ __device__ __forceinline__ bool polar_rv(const V3<R> f[3], Polar<R>& P) {
 
 // V^T b and U (omega x y)
 template <typename R>
-__device__ __forceinline__ V3<R> vt_mul(const Polar<R>& P, V3<R> b) { return mk3(dot(P.v[0], b), dot(P.v[1], b), dot(P.v[2], b)); }
+__device__ __forceinline__ V3<R> vt_mul(const Polar<R>& P, V3<R> b) {
+  return mk3(dot(P.v[0], b), dot<true>(P.v[1], b), dot(P.v[2], b));
+}
 template <typename R>
-__device__ __forceinline__ V3<R> u_mul(const Polar<R>& P, V3<R> y) { return y.x * P.u[0] + y.y * P.u[1] + y.z * P.u[2]; }
+__device__ __forceinline__ V3<R> u_mul(const Polar<R>& P, V3<R> y) { return lin3(y, P.u); }
 
 // w = axial(A - A^T), A = U^T dF V, for dF with columns d_j
 template <typename R>
 __device__ __forceinline__ V3<R> twist_w(const Polar<R>& P, const V3<R> d[3]) {
   V3<R> dv[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) dv[j] = P.v[j].x * d[0] + P.v[j].y * d[1] + P.v[j].z * d[2];
+  dv[0] = lin3(P.v[0].x, P.v[0].y, P.v[0].z, d[0], d[1], d[2]);
+  dv[1] = lin3<true>(P.v[1].x, P.v[1].y, P.v[1].z, d[0], d[1], d[2]);
+  dv[2] = lin3(P.v[2].x, P.v[2].y, P.v[2].z, d[0], d[1], d[2]);
   // A_ij = u_i . (dF v_j)
   return mk3(dot(P.u[2], dv[1]) - dot(P.u[1], dv[2]), dot(P.u[0], dv[2]) - dot(P.u[2], dv[0]),
              dot(P.u[1], dv[0]) - dot(P.u[0], dv[1]));
+}
+
+// sum_i w_i^2 k_i
+template <typename R>
+__device__ __forceinline__ R squares(V3<R> w, V3<R> k) {
+  return std::fma(w.z * w.z, k.z, std::fma(w.x * w.x, k.x, w.y * w.y * k.y));
 }
 
 // Coefficients of the I2 and I3 parts: a2 = 2 V Psi_2, V Psi_3, V Psi_33.
@@ -490,7 +474,7 @@ __device__ __forceinline__ void i23_coeffs(const Kin<R>& k, R vmu, R vlam, R& a2
     nh_coeffs(k, vmu, vlam, vpsi3, vpsi33);
   } else if constexpr (M == kModelSNH) {
     a2 = vmu;
-    vpsi3 = vlam * (k.J - R(1)) - vmu;
+    vpsi3 = std::fma(vlam, k.J - R(1), -vmu);
     vpsi33 = vlam;
   } else {
     a2 = R(2) * vmu;
@@ -520,15 +504,16 @@ __device__ __forceinline__ bool el_grad_diag(const Kin<R>& k, R vmu, R vlam, V3<
     if (!polar_rv(k.f, P)) return false;
     const R a1 = R(-2) * vmu;
     const V3<R> y = vt_mul(P, ba);
-    g = g + a1 * u_mul(P, y);             // Psi_1 R b_a
+    g = fma3(a1, u_mul(P, y), g);         // Psi_1 R b_a
     // diagonal of H1 for coordinate c: w = (U^T e_c) x y
     const V3<R> r0 = mk3(P.u[0].x, P.u[1].x, P.u[2].x);
     const V3<R> r1 = mk3(P.u[0].y, P.u[1].y, P.u[2].y);
     const V3<R> r2 = mk3(P.u[0].z, P.u[1].z, P.u[2].z);
     const V3<R> z0 = cross(r0, y), z1 = cross(r1, y), z2 = cross(r2, y);
-    dg.x += a1 * (z0.x * z0.x * P.ik[0] + z0.y * z0.y * P.ik[1] + z0.z * z0.z * P.ik[2]);
-    dg.y += a1 * (z1.x * z1.x * P.ik[0] + z1.y * z1.y * P.ik[1] + z1.z * z1.z * P.ik[2]);
-    dg.z += a1 * (z2.x * z2.x * P.ik[0] + z2.y * z2.y * P.ik[1] + z2.z * z2.z * P.ik[2]);
+    const V3<R> ik = mk3(P.ik[0], P.ik[1], P.ik[2]);
+    dg.x = std::fma(a1, squares(z0, ik), dg.x);
+    dg.y = std::fma(a1, squares(z1, ik), dg.y);
+    dg.z = std::fma(a1, squares(z2, ik), dg.z);
   }
   return true;
 }
@@ -539,23 +524,23 @@ __device__ __forceinline__ bool el_pHp(const Kin<R>& k, R vmu, R vlam, const V3<
   if (!i23_ok<R, M>(k)) return false;
   R a2, vpsi3, vpsi33;
   i23_coeffs<R, M>(k, vmu, vlam, a2, vpsi3, vpsi33);
-  out = i23_pHp(k, a2, vpsi3, vpsi33, d);
+  out = i23_pHp<M == kModelNH>(k, a2, vpsi3, vpsi33, d);
   if constexpr (M == kModelCorot) {
     Polar<R> P;
     if (!polar_rv(k.f, P)) return false;
     const V3<R> w = twist_w(P, d);
-    out += R(-2) * vmu * (w.x * w.x * P.ik[0] + w.y * w.y * P.ik[1] + w.z * w.z * P.ik[2]);
+    out = std::fma(R(-2) * vmu, squares(w, mk3(P.ik[0], P.ik[1], P.ik[2])), out);
   }
   return true;
 }
 
 // (H_e p)_a without h^2; false outside the model's domain.
-template <typename R, int M>
+template <typename R, int M, bool YX = false>
 __device__ __forceinline__ bool el_Hp(const Kin<R>& k, R vmu, R vlam, const V3<R> d[3], V3<R> ba, V3<R>& out) {
   if (!i23_ok<R, M>(k)) return false;
   R a2, vpsi3, vpsi33;
   i23_coeffs<R, M>(k, vmu, vlam, a2, vpsi3, vpsi33);
-  out = i23_Hp(k, a2, vpsi3, vpsi33, d, ba);
+  out = i23_Hp<YX>(k, a2, vpsi3, vpsi33, d, ba);
   if constexpr (M == kModelCorot) {
     Polar<R> P;
     if (!polar_rv(k.f, P)) return false;

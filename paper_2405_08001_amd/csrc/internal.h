@@ -48,7 +48,7 @@ __host__ __device__ inline double beta_rule(unsigned flags, double gPg, double g
     default: {  // Dai-Kou (0) and Hager-Zhang (4, twice the second term)
       if (yp == 0.0) return 0.0;
       const double c = ((flags >> 4) & 7u) == 4u ? 2.0 : 1.0;
-      b = gPy / yp - c * (yPy / yp) * (pg / yp);
+      b = fma(-(c * (yPy / yp)), pg / yp, gPy / yp);
     }
   }
   return isfinite(b) ? b : 0.0;

@@ -118,7 +118,44 @@ __device__ __forceinline__ void pair_grad_diag_corner(const Args<R>& A, const Cl
   const double tx = ci * c.t.x, ty = ci * c.t.y, tz = ci * c.t.z;
   const double dj = cb * ci * ci;
   val[0] = cg * tx; val[1] = cg * ty; val[2] = cg * tz;
-  val[3] = ca * tx * tx + dj; val[4] = ca * ty * ty + dj; val[5] = ca * tz * tz + dj;
+  val[3] = fma(ca * tx, tx, dj); val[4] = fma(ca * ty, ty, dj); val[5] = fma(ca * tz, tz, dj);
+}
+
+// p^T H p of an active pair from sp = sum_i c_i p_i and t (eq12, eq13)
+__device__ __forceinline__ double pair_pHp(double ca, double cb, V3<double> sp, V3<double> t) {
+  const double st = dot(sp, t);
+  return fma(cb, dot(sp, sp), ca * st * st);
+}
+
+// ---------------------------------------------------------- vertex terms
+// One component of g and of diag(H) without planes and pairs, from the sums
+// sg, sd of the element terms: h^2 times those and the inertia.
+__device__ __forceinline__ double vertex_g(double h2, double sg, double m, double x, double xt) {
+  return fma(h2, sg, m * (x - xt));
+}
+__device__ __forceinline__ double vertex_diag(double h2, double sd, double m) { return fma(h2, sd, m); }
+// a plane's part, component n of its normal: b1, b2 = kappa b', kappa b''
+__device__ __forceinline__ void add_plane(double b1, double b2, double n, double& g, double& d) {
+  g = fma(b1, n, g);
+  d = fma(b2 * n, n, d);
+}
+// The products for beta, one component: g, P g, the previous g, p, and 1 / diag
+__device__ __forceinline__ void add_beta_dots(double g, double pg, double g_prev, double p, double P, double* dots) {
+  const double y = g - g_prev;
+  dots[0] = fma(g, g, dots[0]);
+  dots[1] = fma(g, pg, dots[1]);
+  dots[2] = fma(g * P, y, dots[2]);
+  dots[3] = fma(y, p, dots[3]);
+  dots[4] = fma(y * P, y, dots[4]);
+  dots[5] = fma(p, g, dots[5]);
+}
+
+// ------------------------------------------------------- iteration scalars
+// d^T g of the direction -P g + beta p
+__device__ __forceinline__ double direction_gTp(double beta, double pg, double gPg) { return fma(beta, pg, -gPg); }
+// predicted decrease (Sec. 4.4)
+__device__ __forceinline__ double predicted_dE(double alpha, double gTp, double pHp) {
+  return fma(-(0.5 * alpha * alpha), pHp, -(alpha * gTp));
 }
 
 }  // namespace pncg

@@ -147,7 +147,7 @@ __device__ __forceinline__ bool pair_at(const Args<R>& A, bool pt, const int (&i
   V3<double> X[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) X[i] = pos(iv[i]);
-  c = pt ? closest_pt<true>(X[0], X[1], X[2], X[3]) : closest_ee<true>(X[0], X[1], X[2], X[3]);
+  c = pt ? closest_pt(X[0], X[1], X[2], X[3]) : closest_ee(X[0], X[1], X[2], X[3]);
   if (!(c.d > 0.0)) {
     raise_err(A.status, kErrPenetration);
     return false;
@@ -184,7 +184,7 @@ __device__ __forceinline__ bool pair_dir(const int (&iv)[4], const double (&c)[4
   for (int i = 0; i < 4; ++i) {
     V3<R> g;
     from_word(w[3 * i], g.x); from_word(w[3 * i + 1], g.y); from_word(w[3 * i + 2], g.z);
-    sp = sp + c[i] * cast3<double>(direction(g, p[i], beta));
+    sp = fma3(c[i], cast3<double>(direction(g, p[i], beta)), sp);
   }
   return true;
 }
@@ -471,8 +471,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
           const double aup = (K->A.has_prims && pm > 0.0) ? K->A.dhat / (2.0 * pm) : HUGE_VAL;
           const double alpha = fmin(aup, abar);
           const int hits = aup < abar ? 1 : 0;
-          const double dE = fma(-(0.5 * alpha * alpha), pHp, -(alpha * gTp));
-          const double dmove = alpha * pmv;
+          const double dE = predicted_dE(alpha, gTp, pHp);
           IterScal* o = K->A.scal + k;
           StepStatus* st = K->A.status;
           if (!isfinite(alpha)) {
@@ -485,7 +484,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
             }
           } else {
             const double dE0 = (k == 1) ? dE : run.dE0;
-            const double D = (SELF ? run.Dx : run.D) + dmove;
+            const double D = fma(alpha, pmv, SELF ? run.Dx : run.D);
             int stop = 0, reason = 0;
             if (K->A.term == 0 && dE < K->A.eps * dE0) { stop = 1; reason = 0; }
             else if (k == K->A.iter_max) { stop = 1; reason = 2; }
@@ -576,8 +575,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
     }
     // ---- element gradient and diagonal, summed per vertex; then the vertex
     // terms (vertex_terms), one component to a thread: inertia, planes, pairs;
-    // g, P g = g / diag and 1 / diag.  The fused forms written out are those
-    // the compiler chooses in the per-iteration launches.
+    // g, P g = g / diag and 1 / diag.
     for (int c = 0;; ++c) {
       {
         PHASE;
@@ -685,8 +683,8 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
           tg = tot[j];
           td = tot[3 + j];
         }
-        double gd = fma(h2, double(tg), m * (X[i] - XT[i]));
-        double dd = fma(h2, double(td), m);
+        double gd = vertex_g(h2, double(tg), m, X[i], XT[i]);
+        double dd = vertex_diag(h2, double(td), m);
         if (fl & kSurface) {
           const V3<double> x = at3(X, l);
           for (int a = 0; a < K->A.planes.n; ++a) {
@@ -695,9 +693,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
             if (d < dhat) {
               if (!(d > 0.0)) { raise_err(K->A.status, kErrPenetration); continue; }
               const double b1 = K->A.kappa * barrier_db(d, dhat), b2 = K->A.kappa * barrier_d2b(d, dhat);
-              const double nj = pl[j];
-              gd = fma(b1, nj, gd);
-              dd = fma(b2 * nj, nj, dd);
+              add_plane(b1, b2, pl[j], gd, dd);
               if (j == 0) atomicAdd(&count[k & 1], 1);
             }
           }
@@ -720,9 +716,9 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
           }
           if ((fl & kSurface) && j == 0) {
             const double* XB = LDS_AT(double, xb);
-            const double ex = X[i] - XB[i], ey = X[i + 1] - XB[i + 1], ez = X[i + 2] - XB[i + 2];
+            const V3<double> e = at3(X, l) - at3(XB, l);
             // the square (positive doubles order as their bits; the root is monotonic)
-            const double e2 = fma(ez, ez, fma(ex, ex, ey * ey));
+            const double e2 = dot(e, e);
             if (e2 > 0.0) atomicMax(&moved[k & 1], word(e2));
           }
           if (pending && (fl & kPairVertex)) st1_agent((k & 1) ? K->A.x1 : K->A.x0, own0 + l, j, X[i]);
@@ -755,14 +751,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
           const int i = 3 * ((int)m.y + __popcll(m.x & ((1ull << lane) - 1)));
 #pragma unroll
           for (int j = 0; j < 3; ++j) {
-            const double g = double(gn[i + j]), pgj = double(pg[i + j]), pp = double(p[i + j]), P = Pd[i + j];
-            const double y = g - double(go[i + j]);
-            dots[0] = fma(g, g, dots[0]);
-            dots[1] = fma(g, pgj, dots[1]);
-            dots[2] = fma(g * P, y, dots[2]);
-            dots[3] = fma(y, pp, dots[3]);
-            dots[4] = fma(y * P, y, dots[4]);
-            dots[5] = fma(pp, g, dots[5]);
+            add_beta_dots(double(gn[i + j]), double(pg[i + j]), double(go[i + j]), double(p[i + j]), Pd[i + j], dots);
           }
         }
       }
@@ -848,7 +837,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
         const double gPy = r[2], yp = r[3], yPy = r[4], pg = r[5];
         double beta = 0.0;
         if (k > 0) beta = beta_rule(K->A.flags, gPg, gPy, yp, yPy, pg, run.gPg, run.gTp);
-        double gTp = fma(beta, pg, -gPg);
+        double gTp = direction_gTp(beta, pg, gPg);
         if (!(gTp < 0.0)) {
           restart = 1;
           beta = 0.0;
@@ -931,22 +920,20 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
         for (int v = lblk[vi][4] + (kSplitPasses ? vt - kSBlock : vt); v < v1; v += kSplitPasses ? DB - kSBlock : DB) {
           const int l = dv[v - v0];
           const V3<R> q = at3(p, l);
-          const double px = q.x, py = q.y, pz = q.z;
-          const double p2 = fma(pz, pz, fma(px, px, py * py));
+          const V3<double> pd = cast3<double>(q);
+          const double p2 = dot(pd, pd);
           double vp = Ms[l] * p2;
           if (fls[l] & kSurface) {
             const V3<double> x = at3(X, l);
             for (int a = 0; a < K->A.planes.n; ++a) {
               const double* pl = planes + 4 * a;
               const double d = plane_dist(pl, x), dhat = K->A.dhat;
-              if (d > 0.0 && d < dhat) {
-                const double np = fma(pl[2], pz, fma(pl[0], px, pl[1] * py));
-                vp = fma(K->A.kappa * barrier_d2b(d, dhat) * np, np, vp);
-              }
+              if (d > 0.0 && d < dhat)
+                vp = fma(plane_Hp(K->A.kappa, pl, d, dhat, pd), dot(mk3(pl[0], pl[1], pl[2]), pd), vp);
             }
           }
-          const double pabs = sqrt(p2), pcomp = fmax(fabs(px), fmax(fabs(py), fabs(pz)));
-          acc_pHp += vp;
+          const double pabs = sqrt(p2), pcomp = fmax(fabs(pd.x), fmax(fabs(pd.y), fabs(pd.z)));
+          acc_pHp = sum_rounded(acc_pHp, vp);
           pmv = fmax(pmv, pabs);
           pmc = fmax(pmc, pcomp);
         }
@@ -965,8 +952,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
               const double c[4] = {g->c[0], g->c[1], g->c[2], g->c[3]};
               V3<double> sp;
               if (!pair_dir<R>(iv, c, src, pk, rb, limit, sp)) run.bad = 1;
-              const double st = fdot(sp, mk3(g->t[0], g->t[1], g->t[2]));
-              acc_pHp += fma(g->cb, fdot(sp, sp), g->ca * st * st);
+              acc_pHp += pair_pHp(g->ca, g->cb, sp, mk3(g->t[0], g->t[1], g->t[2]));
             }
           }
         } else {
@@ -987,8 +973,7 @@ __global__ void __launch_bounds__(MAXT) k_persist(KArgs<R>) {
             pair_hess_coefs(pa, c.d, ca, cb);
             V3<double> sp;
             if (!pair_dir<R>(iv, c.c, src, pk, rb, limit, sp)) run.bad = 1;
-            const double st = fdot(sp, c.t);
-            acc_pHp += fma(cb, fdot(sp, sp), ca * st * st);
+            acc_pHp += pair_pHp(ca, cb, sp, c.t);
           }
         }
       }

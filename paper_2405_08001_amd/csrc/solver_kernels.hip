@@ -164,7 +164,7 @@ __device__ FirstPro first_prologue(const Args<R>& A, int k, int mode, double* sh
     fp.work = 0;
     return fp;
   }
-  double alpha = 0.0, dE = 0.0, dmove = 0.0;
+  double alpha = 0.0, dE = 0.0, dmove = 0.0;   // dmove: largest |p| (SPLIT: alpha |p|)
   int hits = 0;
   bool unbounded = false;
   if (!SPLIT) {
@@ -179,8 +179,8 @@ __device__ FirstPro first_prologue(const Args<R>& A, int k, int mode, double* sh
     alpha = fmin(aup, abar);
     hits = aup < abar ? 1 : 0;
     unbounded = !isfinite(alpha);
-    dE = -alpha * gTp - 0.5 * alpha * alpha * pHp;
-    dmove = alpha * pmv;
+    dE = predicted_dE(alpha, gTp, pHp);
+    dmove = pmv;
   } else {
     const ObjScal* os = A.oscal + (size_t)(k - 1) * A.nObj;
     const int kind[4] = {0, 0, 1, 1};
@@ -215,7 +215,8 @@ __device__ FirstPro first_prologue(const Args<R>& A, int k, int mode, double* sh
   const double dE0 = (k == 1) ? dE : prev.dE0;
   // displacement of any surface vertex since the list build: exact at x_{k-1}
   // (measured by the gradient sweep) plus at most alpha |p|_max this update
-  const double D = (A.self ? prev.Dx : prev.D) + dmove;
+  const double Dp = A.self ? prev.Dx : prev.D;
+  const double D = SPLIT ? Dp + dmove : fma(alpha, dmove, Dp);
   int stop = 0, reason = 0;
   if (A.term == 0 && dE < A.eps * dE0) { stop = 1; reason = 0; }
   else if (mode == kModeFinish) { stop = 1; reason = 2; }
@@ -465,16 +466,21 @@ __device__ __forceinline__ bool lane_elem(const Args<R>& A, int code, const Pos&
   return true;
 }
 
-// Vertex terms at x_v: inertia m (x - xt), plane barriers (surface
-// vertices), contact-pair sums (`pairs`: the segmented sums of the vertex's
-// slots, or NULL for the atomic accumulators); returns g and diag in float64.
+// Vertex terms at x_v: the element sums s (gradient, diagonal; times h^2),
+// inertia m (x - xt), plane barriers (surface vertices), contact-pair sums
+// (`pairs`: the segmented sums of the vertex's slots, or NULL for the atomic
+// accumulators); returns g and diag in float64.
 template <typename R>
-__device__ __forceinline__ void vertex_terms(const Args<R>& A, int v, V3<double> x, double (&gd)[3], double (&dd)[3],
-                                             double& nplane, bool zero_acc, const double* pairs = nullptr) {
+__device__ __forceinline__ void vertex_terms(const Args<R>& A, int v, V3<double> x, const R (&s)[6], double (&gd)[3],
+                                             double (&dd)[3], double& nplane, bool zero_acc,
+                                             const double* pairs = nullptr) {
   const double m = A.mass[v];
   V3<double> xt = ld3(A.xt, v);
-  gd[0] += m * (x.x - xt.x); gd[1] += m * (x.y - xt.y); gd[2] += m * (x.z - xt.z);
-  dd[0] += m; dd[1] += m; dd[2] += m;
+  gd[0] = vertex_g(A.h2, double(s[0]), m, x.x, xt.x);
+  gd[1] = vertex_g(A.h2, double(s[1]), m, x.y, xt.y);
+  gd[2] = vertex_g(A.h2, double(s[2]), m, x.z, xt.z);
+#pragma unroll
+  for (int j = 0; j < 3; ++j) dd[j] = vertex_diag(A.h2, double(s[3 + j]), m);
   const uint8_t fl = A.vflag[v];
   if (fl & kSurface) {
     for (int j = 0; j < A.planes.n; ++j) {
@@ -483,8 +489,8 @@ __device__ __forceinline__ void vertex_terms(const Args<R>& A, int v, V3<double>
       if (d < A.dhat) {
         if (!(d > 0.0)) { raise_err(A.status, kErrPenetration); continue; }
         const double b1 = A.kappa * barrier_db(d, A.dhat), b2 = A.kappa * barrier_d2b(d, A.dhat);
-        gd[0] += b1 * pl[0]; gd[1] += b1 * pl[1]; gd[2] += b1 * pl[2];
-        dd[0] += b2 * pl[0] * pl[0]; dd[1] += b2 * pl[1] * pl[1]; dd[2] += b2 * pl[2] * pl[2];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) add_plane(b1, b2, pl[c], gd[c], dd[c]);
         nplane += 1.0;
       }
     }
@@ -569,13 +575,11 @@ __global__ void __launch_bounds__(BS, (GradBlock<R, M>::min_waves)) k_grad(Args<
     }
     const V3<double> x = pos(v);
     if (MODE == kGradFirst && fp.materialize) st3(xcur, v, x);
-    double gd[3] = {A.h2 * double(s[0]), A.h2 * double(s[1]), A.h2 * double(s[2])};
-    double dd[3] = {A.h2 * double(s[3]), A.h2 * double(s[4]), A.h2 * double(s[5])};
-    vertex_terms(A, v, x, gd, dd, dots[6], MODE != kGradQuery, SEG ? prs : nullptr);
+    double gd[3], dd[3];
+    vertex_terms(A, v, x, s, gd, dd, dots[6], MODE != kGradQuery, SEG ? prs : nullptr);
     if ((MODE == kGradDirect || FUSED) && A.self && (A.vflag[v] & kSurface)) {
-      const V3<double> xb = ld3(A.xbuild, v);
-      const double ex = x.x - xb.x, ey = x.y - xb.y, ez = x.z - xb.z;
-      dots[7] = fmax(dots[7], sqrt(ex * ex + ey * ey + ez * ez));
+      const V3<double> e = x - ld3(A.xbuild, v);
+      dots[7] = fmax(dots[7], sqrt(dot(e, e)));
     }
     if (A.vflag[v] & kFixed) {
       gd[0] = gd[1] = gd[2] = 0.0;
@@ -599,30 +603,12 @@ __global__ void __launch_bounds__(BS, (GradBlock<R, M>::min_waves)) k_grad(Args<
     if constexpr (SPLIT) {
       double vd[6] = {0, 0, 0, 0, 0, 0};
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const double P = 1.0 / dd[j];
-        const double y = g3[j] - gp3[j];
-        vd[0] += g3[j] * g3[j];
-        vd[1] += g3[j] * pg3[j];
-        vd[2] += g3[j] * P * y;
-        vd[3] += y * pp3[j];
-        vd[4] += y * P * y;
-        vd[5] += pp3[j] * g3[j];
-      }
+      for (int j = 0; j < 3; ++j) add_beta_dots(g3[j], pg3[j], gp3[j], pp3[j], 1.0 / dd[j], vd);
 #pragma unroll
       for (int i = 0; i < 6; ++i) A.vdots[6 * (size_t)v + i] = vd[i];
     } else {
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const double P = 1.0 / dd[j];
-        const double y = g3[j] - gp3[j];
-        dots[0] += g3[j] * g3[j];
-        dots[1] += g3[j] * pg3[j];
-        dots[2] += g3[j] * P * y;
-        dots[3] += y * pp3[j];
-        dots[4] += y * P * y;
-        dots[5] += pp3[j] * g3[j];
-      }
+      for (int j = 0; j < 3; ++j) add_beta_dots(g3[j], pg3[j], gp3[j], pp3[j], 1.0 / dd[j], dots);
     }
   }
   if (MODE == kGradQuery) return;
@@ -690,7 +676,7 @@ __global__ void __launch_bounds__(BS) k_dir(Args<R> A, int k) {
       const IterScal sp = A.scal[k - 1];
       beta = beta_rule(A.flags, gPg, gPy, yp, yPy, pg, sp.gPg, sp.gTp);
     }
-    gTp = -gPg + beta * pg;
+    gTp = direction_gTp(beta, pg, gPg);
     if (!(gTp < 0.0)) {
       restart = 1;
       beta = 0.0;
@@ -751,27 +737,25 @@ __global__ void __launch_bounds__(BS) k_dir(Args<R> A, int k) {
   for (int v = (int)sv.begin + vt; vert_thread && v < sv.end; v += kSplitPasses ? BS - kSBlock : BS) {
     V3<R> p = direction(ldr<R>(A.pg, v), ldr<R>(pk, v), beta_of(v));
     str<R>(pn, v, p);
-    const double px = p.x, py = p.y, pz = p.z;
-    const double p2 = px * px + py * py + pz * pz;
+    const V3<double> pd = cast3<double>(p);
+    const double p2 = dot(pd, pd);
     double vp = A.mass[v] * p2;
     if ((A.vflag[v] & kSurface) && A.planes.n > 0) {
       const V3<double> x = ld3(xk, v);
       for (int j = 0; j < A.planes.n; ++j) {
         const double* pl = A.planes.p[j];
         const double d = plane_dist(pl, x);
-        if (d > 0.0 && d < A.dhat) {
-          const double np = pl[0] * px + pl[1] * py + pl[2] * pz;
-          vp += A.kappa * barrier_d2b(d, A.dhat) * np * np;
-        }
+        if (d > 0.0 && d < A.dhat)
+          vp = fma(plane_Hp(A.kappa, pl, d, A.dhat, pd), dot(mk3(pl[0], pl[1], pl[2]), pd), vp);
       }
     }
-    const double pabs = sqrt(p2), pcomp = fmax(fabs(px), fmax(fabs(py), fabs(pz)));
+    const double pabs = sqrt(p2), pcomp = fmax(fabs(pd.x), fmax(fabs(pd.y), fabs(pd.z)));
     if constexpr (SPLIT) {
       A.vphp[3 * (size_t)v] = vp;
       A.vphp[3 * (size_t)v + 1] = pabs;
       A.vphp[3 * (size_t)v + 2] = pcomp;
     } else {
-      acc_pHp += vp;
+      acc_pHp = sum_rounded(acc_pHp, vp);
       pmv = fmax(pmv, pabs);
       pmc = fmax(pmc, pcomp);
     }
@@ -814,10 +798,9 @@ __global__ void __launch_bounds__(BS) k_dir(Args<R> A, int k) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           V3<R> p = direction(ldr<R>(A.pg, iv[i]), ldr<R>(pk, iv[i]), beta_of(iv[i]));
-          sp = sp + c.c[i] * cast3<double>(p);
+          sp = fma3(c.c[i], cast3<double>(p), sp);
         }
-        const double st = dot(sp, c.t);
-        acc_pHp += ca * st * st + cb * dot(sp, sp);
+        acc_pHp += pair_pHp(ca, cb, sp, c.t);
       }
     });
   }
@@ -1073,7 +1056,7 @@ __global__ void __launch_bounds__(kSBlock) k_hvp(Args<R> A, double* out_hp, doub
       V3<R> d[3];
       dF_cols(rec.B, ldr<R>(A.p0, rec.v[0]), ldr<R>(A.p0, rec.v[1]), ldr<R>(A.p0, rec.v[2]), ldr<R>(A.p0, rec.v[3]), d);
       V3<R> hp;
-      if (el_Hp<R, M>(kin, rec.vmu, rec.vlam, d, shape_vec(rec.B, a), hp)) {
+      if (el_Hp<R, M, M == kModelNH>(kin, rec.vmu, rec.vlam, d, shape_vec(rec.B, a), hp)) {
         s[0] = hp.x; s[1] = hp.y; s[2] = hp.z;
       } else {
         raise_err(A.status, kErrInverted);

@@ -157,6 +157,17 @@ __device__ __forceinline__ double plane_dist(const double* pl, V3<double> x) {
   return ((pl[0] * x.x + pl[1] * x.y) + pl[2] * x.z) - pl[3];
 }
 
+// kappa b''(d) (n . p): times n, the plane's part of H p; times n . p, of p^T H p
+__device__ __forceinline__ double plane_Hp(double kappa, const double* pl, double d, double dhat, V3<double> p) {
+  return kappa * barrier_d2b(d, dhat) * dot(mk3(pl[0], pl[1], pl[2]), p);
+}
+
+// a + b, not fused with the product that either may be
+__device__ __forceinline__ double sum_rounded(double a, double b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+
 __device__ __forceinline__ void raise_err(StepStatus* st, int bit) { atomicOr(&st->err, bit); }
 
 // x of iteration k, either materialised in x[k & 1] or, inside the launch
