@@ -272,13 +272,16 @@ int pncg_set_tuning(pncg_ctx* ctx, double skin, int32_t chunk);
 /* The persistent kernels (the iterations of a step, and of an adjoint's CG,
  * in one launch): up to one workgroup on every compute unit, with most of its
  * LDS, which meet through memory in each iteration and so have to be resident
- * together.  A launch whose workgroups do not fit beside those of this
- * process's other contexts is not made; the iterations are launched one by one
- * then.  Where something else holds compute units (other kernels on the
- * device, another process) the workgroups wait for one another, up to
- * max_wait_us in a meeting; a launch that waits longer writes no outputs, the
- * call starts again with the iterations launched one by one, and so do this
- * context's next 64 steps or adjoints.  Both forms give the same bits (a step
+ * together.  Launches of this process's contexts that do not fit beside each
+ * other on a device take turns (a turn is a step, up to a pause for a list
+ * rebuild, or 512 iterations), so calls on several threads wait for each
+ * other (up to 200 ms, then the iterations are launched one by one); other
+ * kernels on the device mostly wait for the end of a launch too.  Where
+ * something else holds compute units (a batch, other kernels on the device,
+ * another process) the workgroups wait for one another, up to max_wait_us in a
+ * meeting; a launch that waits longer writes no outputs, the call starts again
+ * with the iterations launched one by one, and so do this context's next 64
+ * steps or adjoints.  Both forms give the same bits (a step
  * that had rebuilt the list of pairs by then starts again on a list of its
  * own, whose sums may round differently).  The kernels' tables are built by
  * the first step or adjoint after pncg_set_mesh that can use them; without

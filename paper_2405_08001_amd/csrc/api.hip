@@ -10,7 +10,9 @@
 // chunks (to stop, or to rebuild the candidate list when the accumulated
 // displacement bound exceeds half the skin).
 #include <algorithm>
+#include <chrono>
 #include <climits>
+#include <condition_variable>
 #include <mutex>
 #include <new>
 #include <cmath>
@@ -69,30 +71,57 @@ hipError_t scratch_address(int device, void** out) {
   return hipSuccess;
 }
 
-// Compute units that persistent iteration launches of this process hold on
-// each device.  Such a launch needs all its blocks (at most one per compute
-// unit) resident at once, so launches whose blocks add up to no more than the
-// device's compute units can overlap; one that would not fit beside those in
-// flight uses the per-iteration launches instead (same bits).
-std::mutex g_units_mu;
-int g_units_used[kMaxDevices] = {0};
+// Compute units that persistent launches of this process hold on each device.
+// Such a launch needs all its blocks (at most one per compute unit) resident at
+// once, so launches whose blocks add up to no more than the device's compute
+// units can overlap; one that would not fit beside those in flight waits for
+// its turn, in the order in which they asked.  (A launch per iteration would
+// wait for the same compute units again and again: a 1,296-tet step beside the
+// steps of a 30,000-tet context took 3.8 ms so, and takes 1.06 in turn.)
+// Between asking and giving back a thread waits for nothing but its own stream;
+// should that wait for this thread's caller in turn, the asking ends after
+// kTurnMs and the iterations are launched one by one.
+constexpr int kTurnMs = 200;   // a turn of 512 iterations takes up to 15 ms
+struct Units {
+  struct Ask {
+    Ask* next = nullptr;
+  };
+  std::mutex mu;
+  std::condition_variable turn;
+  int used = 0;
+  Ask* first = nullptr;   // asking, in order
+};
+Units g_units[kMaxDevices];
 
 struct UnitsHeld {
   int device = 0, n = 0;
   ~UnitsHeld() { release(); }
   bool acquire(int dev, int blocks, int units) {
-    std::lock_guard<std::mutex> lock(g_units_mu);
-    if (dev < 0 || dev >= kMaxDevices || g_units_used[dev] + blocks > units) return false;
-    g_units_used[dev] += blocks;
+    if (dev < 0 || dev >= kMaxDevices || blocks > units) return false;
+    Units& u = g_units[dev];
+    std::unique_lock<std::mutex> lock(u.mu);
+    Units::Ask me;
+    Units::Ask** at = &u.first;
+    while (*at) at = &(*at)->next;
+    *at = &me;
+    const bool mine = u.turn.wait_for(lock, std::chrono::milliseconds(kTurnMs),
+                                      [&] { return u.first == &me && u.used + blocks <= units; });
+    for (at = &u.first; *at != &me;) at = &(*at)->next;
+    *at = me.next;
+    u.turn.notify_all();
+    if (!mine) return false;
+    u.used += blocks;
     device = dev;
     n = blocks;
     return true;
   }
   void release() {
     if (!n) return;
-    std::lock_guard<std::mutex> lock(g_units_mu);
-    g_units_used[device] -= n;
+    Units& u = g_units[device];
+    std::lock_guard<std::mutex> lock(u.mu);
+    u.used -= n;
     n = 0;
+    u.turn.notify_all();
   }
 };
 
@@ -1300,12 +1329,15 @@ int adjoint_impl(pncg_ctx* c, const double* x1, double h, const double* xbar, co
   const int last = fused ? cg_max + 1 : cg_max;   // the launch that reports the end at the latest
   // the persistent kernel where it can take the iterations (as in the steps)
   UnitsHeld held;
-  bool persist = fused && cg_persist_usable(c, A) && held.acquire(c->device, c->cg_persist.P.blocks, c->units);
+  bool persist = fused && cg_persist_usable(c, A);
   while (true) {
     if (warm) HIPCHK(c, hipMemsetAsync(&c->d_cgst->stopped, 0, sizeof(int), c->stream));
     launch_adj_init(A, C, xbar, vbar, warm, c->stream);
     int k = 0, chunk = 16;
     while (true) {
+      // (a turn per launch; one that follows another and gets none goes ahead
+      // all the same, since its meetings are bounded)
+      persist = persist && (held.acquire(c->device, c->cg_persist.P.blocks, c->units) || k > 0);
       const int kend = std::min(k + (persist ? kPersistMaxIters : chunk), last + 1);
       if (persist) {
         launch_cg_persist(A, C, c->cg_persist, k, c->stream);
@@ -1314,13 +1346,13 @@ int adjoint_impl(pncg_ctx* c, const double* x1, double h, const double* xbar, co
         for (int j = k; j < kend; ++j) launch_cg_iteration(A, C, j, fused, c->stream);
       HIPCHK(c, hipMemcpyAsync(c->h_cgst, c->d_cgst, sizeof(CgStatus), hipMemcpyDeviceToHost, c->stream));
       if ((rc = sync(c))) return rc;
+      held.release();
       if (c->h_cgst->stopped || c->h_cgst->sync) break;
       if (kend > last) return fail(c, PNCG_E_HIP, "adjoint CG did not report its end");
       k = kend;
       chunk = std::min(chunk * 2, 256);
     }
     if (!persist) break;
-    held.release();
     if (!c->h_cgst->sync) {
       // lambda is in the other buffer
       std::swap(c->d_lam, c->d_r);
