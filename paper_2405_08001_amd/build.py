@@ -10,7 +10,7 @@ float64/float32 global atomics are emitted as hardware atomics
 machine-level loop-invariant code motion: their loops hold a whole iteration,
 and the constants and addresses hoisted out cost the step kernel 30 to 70 vector
 registers of the 128 (without: 62-127 and no spill but in the contact forms,
-which spill up to 4 in float and 26 in double).
+which spill up to 4 in float and 22 in double).
 """
 from __future__ import annotations
 

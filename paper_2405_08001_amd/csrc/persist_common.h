@@ -24,9 +24,6 @@ __device__ __forceinline__ void st_agent(u64* p, u64 v) {
 }
 __device__ __forceinline__ u64 full(u64 v) { return v == kEmpty ? v ^ 1 : v; }
 __device__ __forceinline__ u64 word(double a) { return (u64)__double_as_longlong(a); }
-__device__ __forceinline__ u64 word(float a, float b) {
-  return (u64)(unsigned)__float_as_int(a) | ((u64)(unsigned)__float_as_int(b) << 32);
-}
 __device__ __forceinline__ double as_double(u64 w) { return __longlong_as_double((long long)w); }
 __device__ __forceinline__ float lo_float(u64 w) { return __int_as_float((int)(unsigned)w); }
 __device__ __forceinline__ float hi_float(u64 w) { return __int_as_float((int)(unsigned)(w >> 32)); }
