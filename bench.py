@@ -15,10 +15,16 @@ HIP events (profiling): the segmented pair scatter makes all three passes
 follow the same trajectory bit for bit.
 
 One JSON line is printed.  Besides the throughput it carries:
-  roofline      the dominant kernel's algorithmic bytes per launch (the
-                per-tet / per-vertex / per-pair byte model) over its average
-                launch time: from HIP events on the library's stream in the
-                profiled pass, and from the rocprofv3 summary committed in
+  roofline      the dominant kernel of the timed frames (the persistent
+                iteration kernel where they ran it): its algorithmic bytes per
+                launch (the per-tet / per-vertex / per-pair byte model) over
+                the timed frames' time per launch, which holds the list
+                rebuilds and the host's part too.  The memory rate is not what
+                bounds it: the blocks keep the mesh in LDS and wait for two
+                device-wide meetings per iteration
+  roofline_launches  the same for the dominant launch of the profiled pass,
+                which launches each iteration: from HIP events on the
+                library's stream, and from the rocprofv3 summary committed in
                 profiles/ (when it was made from the current kernel sources)
   iter_roofline the whole iteration's algorithmic bytes times iterations/s
   fp64          the plain float64 form over the same frames
@@ -83,7 +89,8 @@ KERNEL_NAMES = {"grad": "k_grad<float, 0, false, 0, true,", "dir": "k_dir<float,
                 "narrow": "k_narrow<float, false>"}
 KERNEL_TIMES = os.path.join(ROOT, "profiles", "kernel_times.json")
 CALIB_BYTES = 256 << 20          # the calibration copy reads and writes this many bytes
-SOLVER_SOURCES = ("solver_kernels.hip", "iteration_common.h", "sweep_common.h", "device_math.h", "internal.h")
+SOLVER_SOURCES = ("solver_kernels.hip", "iteration_common.h", "sweep_common.h", "device_math.h", "internal.h",
+                  "persist.hip", "persist.h", "persist_common.h", "persist_tables.hip")
 
 
 def solver_source_hash():
@@ -188,10 +195,11 @@ def trace_gaps(trace_csv, window_json, top=12):
     for clock in win["start"]:
         t0, t1 = win["start"][clock], win["end"][clock]
         sel = [r for r in rows if int(r["Start_Timestamp"]) >= t0 and int(r["End_Timestamp"]) <= t1]
-        n = sum(1 for r in sel if "k_grad" in r["Kernel_Name"])
+        n = sum(1 for r in sel if "k_grad" in r["Kernel_Name"] or "k_persist<" in r["Kernel_Name"])
         if best is None or n > best[0]:
             best = (n, clock, sel)
-    n_grad, clock, sel = best
+    _, clock, sel = best
+    n_grad, n_persist = (sum(1 for r in sel if k in r["Kernel_Name"]) for k in ("k_grad", "k_persist<"))
     if len(sel) < 2:
         raise SystemExit("no kernel of the trace falls inside the window")
     span = int(sel[-1]["End_Timestamp"]) - int(sel[0]["Start_Timestamp"])
@@ -205,7 +213,10 @@ def trace_gaps(trace_csv, window_json, top=12):
         c[1] += g
     idle = span - busy
     top_gaps = sorted(gaps.items(), key=lambda kv: -kv[1][1])[:top]
-    return {"clock": clock, "kernels": len(sel), "grad_launches": n_grad, "frames": win["frames"],
+    return {"clock": clock, "kernels": len(sel), "grad_launches": n_grad,
+            "persist_launches": n_persist,
+            "persist_us": round(sum(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]) for r in sel
+                                    if "k_persist<" in r["Kernel_Name"]) / 1e3, 1), "frames": win["frames"],
             "iters": win["iters"], "span_us": round(span / 1e3, 1), "busy_us": round(busy / 1e3, 1),
             "idle_frac": round(idle / span, 4), "idle_us_per_frame": round(idle / 1e3 / win["frames"], 1),
             "idle_us_per_iter": round(idle / 1e3 / max(win["iters"], 1), 2),
@@ -263,6 +274,7 @@ def run(sc, precision, settle, warmup, steps, model="nh", profile=True, per_call
     # the same trajectory bit for bit
     ctx.pncg_set_tuning(0.0, 0)
     torch.cuda.synchronize()
+    persist0 = ctx.pncg_get_persistent()[0]
     clocks0 = _clocks()
     t0 = time.perf_counter()
     sts, _ = ctx.pncg_run_dev(x, v, sc.h, steps)
@@ -276,6 +288,7 @@ def run(sc, precision, settle, warmup, steps, model="nh", profile=True, per_call
     reb = sum(st["rebuilds"] for st in sts)
     out = dict(seconds=dt, iters=iters, frames=steps, mean_active=act / steps, mean_cand=cand / steps,
                rebuilds_per_frame=reb / steps, state=state, stats=sts,
+               persist_launches=ctx.pncg_get_persistent()[0] - persist0,
                window={"start": clocks0, "end": clocks1, "frames": steps, "iters": iters})
     if per_call:
         # the same frames through one Python call per step
@@ -668,6 +681,21 @@ def kernel_roofline(kern, prof, sc, r, precision="mixed"):
     return out
 
 
+def persist_roofline(sc, r):
+    """The persistent kernel's: the iterations' algorithmic bytes per launch
+    over the timed frames' time per launch (which holds the list rebuilds and
+    the host's part too; no average over other frames would do, since the
+    iterations per launch differ)."""
+    bt, bv, ba, bq = BYTES["iter"]["mixed"]
+    n = r["persist_launches"]
+    nbytes = (bt * sc.nT + bv * sc.nV + ba * r["mean_active"] + bq * r["mean_cand"]) * r["iters"] / n
+    us = 1e6 * r["seconds"] / n
+    return {"bound": "hbm", "kernel": "persist", "achieved": round(nbytes / us / 1e3, 1), "peak": HBM_PEAK / 1e9,
+            "unit": "GB/s", "frac": round(nbytes / (us * 1e-6) / HBM_PEAK, 4), "bytes_per_launch": int(nbytes),
+            "avg_launch_us": round(us, 3), "launches": n, "iters_per_launch": round(r["iters"] / n, 2),
+            "timing": "the timed frames, per launch"}
+
+
 def summarize(sc, r, precision):
     ips = r["iters"] / r["seconds"]
     bt, bv, ba, bq = BYTES["iter"][precision]
@@ -836,7 +864,10 @@ def main():
     head = summarize(sc, m, "mixed")
     prof = {k: v for k, v in m["prof"].items() if v[1] > 0}
     kern = max((k for k in prof if k in KERNEL_BYTES), key=lambda k: prof[k][0])
-    roof = kernel_roofline(kern, prof, sc, m)
+    roof_launches = kernel_roofline(kern, prof, sc, m)
+    roof = roof_launches
+    if m["persist_launches"] > 0:
+        kern, roof = "persist", persist_roofline(sc, m)
     traffic = None
     tpath = os.path.join(ROOT, "profiles", "traffic.json")
     if os.path.exists(tpath):
@@ -872,6 +903,7 @@ def main():
         "per_call": head.get("per_call"),
         "us_per_iter": head["us_per_iter"],
         "roofline": roof,
+        "roofline_launches": roof_launches,
         "iter_roofline": head["iter_roofline"],
         "kernels_us_avg": head.get("kernels_us_avg"),
         "kernels_launches": head.get("kernels_launches"),
