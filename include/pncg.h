@@ -592,11 +592,13 @@ int pncg_batch_run(pncg_batch* b, double* x_dev, double* v_dev, double h,
 int pncg_batch_stats(pncg_batch* b, int32_t* iters, int32_t* reason,
                      int64_t* iters_total);
 
-/* Time reps steps from (x_dev, v_dev) at each workgroup size in four
- * modes (device memory; LDS staging; LDS staging with large scenes split
- * over up to 2, or up to 8, workgroups) and keep the fastest (its workgroup size written
- * to *block_out if non-NULL; the rest by pncg_batch_get_config).  The state is not modified;
- * iters_total advances by the timed steps. */
+/* Time reps steps that follow the first step from (x_dev, v_dev), at each
+ * workgroup size in four modes (device memory; LDS staging; LDS staging with
+ * large scenes split over up to 2, or up to 8, workgroups) and keep the fastest
+ * (its workgroup size written to *block_out if non-NULL; the rest by
+ * pncg_batch_get_config).  The state is not modified; iters_total advances by
+ * every step taken here.  E_PENETRATION / E_INVERTED if (x_dev, v_dev) itself
+ * is infeasible; a step that the timing alone reaches raises no error. */
 int pncg_batch_autotune(pncg_batch* b, const double* x_dev,
                         const double* v_dev, double h, int32_t reps,
                         int32_t* block_out);

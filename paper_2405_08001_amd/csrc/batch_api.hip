@@ -623,9 +623,24 @@ int pncg_batch_stats(pncg_batch* b, int32_t* iters, int32_t* reason, int64_t* it
 int pncg_batch_autotune(pncg_batch* b, const double* x, const double* v, double h, int32_t reps, int32_t* block_out) {
   if (!b || !x || !v || reps < 1) return bfail(b, PNCG_E_INVAL, "bad arguments");
   BCHK(b, hipSetDevice(b->device));
-  hipEvent_t e0, e1;
-  BCHK(b, hipEventCreate(&e0));
-  BCHK(b, hipEventCreate(&e1));
+  // The timed steps follow one another from (x, v), as the steps of a run do:
+  // on one state alone the settings can tie that a run's states tell apart
+  // (256 scenes ten steps into their fall: 10.13 ms at 1024 threads with teams
+  // of up to 2 and 10.18 at 512 with up to 8, but 10.3 and 11.2 from the next
+  // step on).
+  struct Scratch {
+    double* st = nullptr;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    ~Scratch() {
+      if (st) (void)hipFree(st);
+      if (e0) (void)hipEventDestroy(e0);
+      if (e1) (void)hipEventDestroy(e1);
+    }
+  } q;
+  const size_t n3 = 3 * (size_t)b->nV;
+  BCHK(b, hipMalloc(reinterpret_cast<void**>(&q.st), sizeof(double) * 2 * n3));
+  BCHK(b, hipEventCreate(&q.e0));
+  BCHK(b, hipEventCreate(&q.e1));
   float best = 1e30f;
   int best_b = b->block, best_t = b->max_team;
   bool best_l = b->lds;
@@ -639,13 +654,18 @@ int pncg_batch_autotune(pncg_batch* b, const double* x, const double* v, double 
       b->max_team = modes[m][1];
       int rc = ensure_schedule(b);
       if (rc) return rc;
-      launch(b, h, x, v, b->d_xa, b->d_va);  // warm-up
-      BCHK(b, hipEventRecord(e0, b->stream));
-      for (int r = 0; r < reps; ++r) launch(b, h, x, v, b->d_xa, b->d_va);
-      BCHK(b, hipEventRecord(e1, b->stream));
-      BCHK(b, hipEventSynchronize(e1));
+      double *xa = b->d_xa, *va = b->d_va, *xb = q.st, *vb = q.st + n3;
+      launch(b, h, x, v, xa, va);  // warm-up, and the first of the steps
+      BCHK(b, hipEventRecord(q.e0, b->stream));
+      for (int r = 0; r < reps; ++r) {
+        launch(b, h, xa, va, xb, vb);
+        std::swap(xa, xb);
+        std::swap(va, vb);
+      }
+      BCHK(b, hipEventRecord(q.e1, b->stream));
+      BCHK(b, hipEventSynchronize(q.e1));
       float ms = 0.0f;
-      BCHK(b, hipEventElapsedTime(&ms, e0, e1));
+      BCHK(b, hipEventElapsedTime(&ms, q.e0, q.e1));
       if (ms < best) {
         best = ms;
         best_b = kBlocks[i];
@@ -653,8 +673,9 @@ int pncg_batch_autotune(pncg_batch* b, const double* x, const double* v, double 
         best_t = b->max_team;
       }
     }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
+  int err = 0;
+  BCHK(b, hipMemcpyAsync(&err, b->d_err, sizeof(int), hipMemcpyDeviceToHost, b->stream));
+  BCHK(b, hipStreamSynchronize(b->stream));
   b->block = best_b;
   b->lds = best_l;
   b->max_team = best_t;
@@ -662,6 +683,12 @@ int pncg_batch_autotune(pncg_batch* b, const double* x, const double* v, double 
   int rc = ensure_schedule(b);
   if (rc) return rc;
   if (block_out) *block_out = best_b;
+  if (err & kErrTeam) return check_err(b);
+  // what counts is whether (x, v) itself is feasible, not a later state; the
+  // statistics are those of its step
+  BCHK(b, hipMemsetAsync(b->d_err, 0, sizeof(int), b->stream));
+  launch(b, h, x, v, b->d_xa, b->d_va);
+  BCHK(b, hipGetLastError());
   return check_err(b);
 }
 
