@@ -36,10 +36,11 @@
 // gathering block per sum.
 //
 // Waits.  All blocks must be resident: the grid has at most one block per
-// compute unit, and the host counts the compute units that such launches of
-// the process hold.  A wait is bounded by the clock all the same; a launch
-// that runs out raises kErrSync, writes nothing, and the host runs the step
-// again with the per-iteration launches, which give the same bits.
+// compute unit, and launches of several contexts of a process that would not
+// fit beside each other take turns (UnitsHeld).  A wait is bounded by the clock
+// all the same; a launch that runs out raises kErrSync, writes nothing, and the
+// host runs the step again with the per-iteration launches, which give the same
+// bits.
 //
 // Measured, us per pass: by launches, here with element terms by lane, by tet:
 //   1,296 tets float64, 20 iterations           446   287   282
