@@ -244,7 +244,8 @@ struct pncg_ctx {
   long long work_cap = 0;
   int grid = 1;
   // persistent kernels: tables and exchange buffers (build_persist)
-  bool persist_built = false;   // built, or found that there can be none
+  bool persist_built = false;
+  bool persist_asked[3] = {false, false, false};   // tables asked for, by who (persist_build): not to be tried again
   bool persist_ok[2] = {false, false};   // the mesh has tables (by element form, see PersistTables)
   int persist_off = 0;          // after a timed-out meeting: steps that still use the per-iteration launches
   long long persist_wait = kPersistWaitUs * kTicksPerUs;   // PersistArgs::limit
@@ -782,14 +783,15 @@ int read_status(pncg_ctx* c) {
 // 13,000 and 3.5 ms at 110,000.  Without memory for them, on the host or the
 // device, or where a block's share does not fit in LDS, the iterations are
 // launched one by one.
-void build_persist(pncg_ctx* c) {
-  c->persist_built = true;
+void build_persist(pncg_ctx* c, int who) {
+  if (c->persist_built || c->persist_asked[who]) return;
+  c->persist_asked[who] = true;
   unsigned char* base = nullptr;
   try {
     PersistTables T;
-    persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, c->precision == PNCG_FP64,
-                  c->nF + c->nE > 0, T);
-    if (!T.ok[0] && !T.ok[1]) return;
+    if (!persist_build(c->nV, c->nT, c->tets.data(), c->inc, c->inc_vert, c->grid, c->precision == PNCG_FP64,
+                       c->nF + c->nE > 0, who, T))
+      return;
     PersistArgs& P = T.form[0];
     // first the sizes, then the addresses and copies
     size_t bytes = 0;
@@ -850,6 +852,7 @@ void build_persist(pncg_ctx* c) {
     c->cg_persist = T.cg;
     c->cg_persist.P = P;
     c->cg_persist_ok = T.cg_ok;
+    c->persist_built = true;
   } catch (const std::bad_alloc&) {
   }
 }
@@ -867,7 +870,7 @@ bool persist_wanted(const pncg_ctx* c, const Args<R>& A) {
 template <typename R>
 bool persist_usable(pncg_ctx* c, const Args<R>& A) {
   if (!c->persist_built) {
-    if (c->noalloc) return false;
+    if (c->noalloc || c->persist_asked[persist_form(A.model)]) return false;
     if (A.self) {
       // dense contact keeps to the launches; before a first step's status is
       // in, the list itself has to be asked
@@ -875,7 +878,7 @@ bool persist_usable(pncg_ctx* c, const Args<R>& A) {
           hipStreamSynchronize(c->stream) != hipSuccess || 4 * c->h_n[0] > (long long)c->nV)
         return false;
     }
-    build_persist(c);
+    build_persist(c, persist_form(A.model));
   }
   if (!c->persist_ok[persist_form(A.model)]) return false;
   signed char& fit = c->persist_fit[A.model][A.self];
@@ -1274,7 +1277,7 @@ int ensure_adjoint(pncg_ctx* c, int cg_max) {
 // Whether the adjoint's CG iterations can run in their persistent kernel.
 bool cg_persist_usable(pncg_ctx* c, const Args<double>& A) {
   if (A.model == kModelCorot || c->profiling || c->persist_off > 0) return false;
-  if (!c->persist_built) build_persist(c);
+  build_persist(c, kForAdjoint);
   if (!c->cg_persist_ok) return false;
   signed char& fit = c->cg_persist_fit[A.model];
   if (fit < 0) {
@@ -1568,6 +1571,7 @@ int pncg_set_mesh(pncg_ctx* c, int32_t nV, const double* X, int32_t nT, const in
   for (void* p : c->allocs) (void)hipFree(p);
   c->allocs.clear();
   c->persist_built = c->persist_ok[0] = c->persist_ok[1] = c->cg_persist_ok = false;
+  for (bool& a : c->persist_asked) a = false;
   c->persist_off = 0;
   c->persist_launches = c->persist_timeouts = 0;
   for (auto& m : c->cg_persist_fit) m = -1;

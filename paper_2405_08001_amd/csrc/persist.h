@@ -78,6 +78,12 @@ struct PersistArgs {
 constexpr unsigned short kNone = 0xffff;
 constexpr unsigned short kLaneVert = 0x7fff, kLaneLast = 0x8000;   // vertex of a lane (kLaneVert: none); its last lane
 constexpr int kMaxChunks = 8;
+// Most chunks of a step's blocks; the adjoint takes kMaxChunks.  25 iterations,
+// here and by launches: 907 and 977 us (118,000 tets float64) and 859 and 975
+// us (179,000 mixed) with 6 chunks, 989 and 969 us (125,000 float64) and 1,047
+// and 1,048 us (206,000 mixed) with 8.  CG iterations, 125,000 tets, 8 chunks:
+// 8.9 and 10.5 ms.
+constexpr int kStepChunks = 6;
 constexpr int kRec = 12;              // reals of an element record in LDS (11, padded to 16 bytes)
 constexpr int kRunPartials = 256;     // pair entries of a block with run partials in LDS
 constexpr size_t kPairGeom = 88;      // bytes of a PairGeom (persist.hip); one wave of them per logical block
@@ -125,11 +131,14 @@ struct PersistTables {
   std::vector<unsigned short> dvert;
   PersistArgs form[2];
   CgPersist cg;         // layout only
-  bool ok[2], cg_ok;    // a block's share fits in LDS
+  bool ok[2], cg_ok;    // which can use them: a block's share fits in LDS
 };
 inline int persist_form(int model) { return model == kModelCorot ? 1 : 0; }
-void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc, const std::vector<int>& inc_vert,
-                   int grid, bool fp64, bool self, PersistTables& T);
+// Who asks for the tables: a step, by its element form, or the adjoint.
+constexpr int kForAdjoint = 2;
+// False, and no tables, where who asks (persist_form, kForAdjoint) could not use them.
+bool persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc, const std::vector<int>& inc_vert,
+                   int grid, bool fp64, bool self, int who, PersistTables& T);
 // Fill the exchange buffers with the empty mark and reset the ring.
 void persist_clear(const PersistArgs& P, int nV, hipStream_t s);
 // Iterations [k0, k0 + kPersistMaxIters) of a step, or up to its stop, pause or

@@ -82,8 +82,8 @@ struct Numbers {
 
 }  // namespace
 
-void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc, const std::vector<int>& inc_vert,
-                   int grid, bool fp64, bool self, PersistTables& T) {
+bool persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc, const std::vector<int>& inc_vert,
+                   int grid, bool fp64, bool self, int who, PersistTables& T) {
   const int nWaves = (int)(inc.size() / kWave);
   T = PersistTables{};
   PersistArgs P{};
@@ -94,7 +94,7 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
   const int blocks = P.blocks;
   const unsigned real = fp64 ? 8 : 4;
   // a share of the mesh that cannot fit even without its neighbours
-  if ((size_t)(nV / blocks) * (104 + 12 * real) + (size_t)(nT / blocks) * 12 > kPersistLds) return;
+  if ((size_t)(nV / blocks) * (104 + 12 * real) + (size_t)(nT / blocks) * 12 > kPersistLds) return false;
   // the tables of 4000 tets take about half a millisecond on one core
   const int workers = std::min({blocks, 1 + nT / 4000, 8});
   T.blk.resize(blocks);
@@ -252,7 +252,7 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
     number(0, at);
     caps(T.blk[at]);
     PersistArgs A = P;
-    if (!layout(A, 8, 0, 0) && !layout(A, 0, 0, 0)) return;
+    if (!layout(A, who == kForAdjoint ? kMaxChunks : who == 0 ? kStepChunks : 0, 0, 0)) return false;
     done = at;
   }
   while ((int)marks.size() < workers) add_marks();
@@ -267,24 +267,25 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
     caps(B);
   }
   // 16-bit local numbers; a lane's words also hold the corner (two bits) and the last-lane mark
-  if (cap_loc >= kLaneVert || cap_tet >= (kNone >> 2)) return;
+  if (cap_loc >= kLaneVert || cap_tet >= (kNone >> 2)) return false;
   P.cap_own = (int)cap_own;
 
   T.form[0] = T.form[1] = P;
   // one pass over the waves before the records in LDS, then as few chunks as fit
-  static const int order[][2] = {{1, 1}, {2, 1}, {1, 0}, {2, 0}, {3, 0}, {4, 0}, {6, 0}, {8, 0}};
+  static const int order[][2] = {{1, 1}, {2, 1}, {1, 0}, {2, 0}, {3, 0}, {4, 0}, {kStepChunks, 0}, {kMaxChunks, 0}};
+  bool by_tet = false;
   for (const auto& t : order)
-    if (!T.ok[0] && (layout(T.form[0], t[0], t[1], 1) || layout(T.form[0], t[0], t[1], 0))) {
+    if (!by_tet && (layout(T.form[0], t[0], t[1], 1) || layout(T.form[0], t[0], t[1], 0))) {
       T.form[0].chunks = t[0];
-      T.ok[0] = true;
+      by_tet = true;
     }
+  T.ok[0] = by_tet && T.form[0].chunks <= kStepChunks;
   for (int in_lds = 1; in_lds >= 0 && !T.ok[1]; --in_lds)
     T.ok[1] = layout(T.form[1], 0, in_lds, 1) || layout(T.form[1], 0, in_lds, 0);
-  if (!T.ok[0] && !T.ok[1]) return;
 
   // the chunks' tets
   const int nc = T.form[0].chunks;
-  if (T.ok[0] && fp64) {
+  if (by_tet && fp64) {
     size_t o = 0;
     auto put = [&](unsigned& f, size_t bytes, size_t align) {
       o = (o + align - 1) / align * align;
@@ -312,10 +313,11 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
     T.cg.lds = o;
     T.cg_ok = o <= kCgLds;
   }
+  if (!(who == kForAdjoint ? T.cg_ok : T.ok[who])) return false;
   Lists<PersistEntry> entry(blocks);
   Lists<ushort2> seg(blocks);
   std::vector<int4> chunk((size_t)blocks * (nc + 1), make_int4(0, 0, 0, 0));
-  if (T.ok[0]) {
+  if (T.ok[0] || T.cg_ok) {
     for (int p = 0; p < blocks; ++p) {
       entry.room(p, std::min<size_t>((size_t)T.blk[p].nw * kWave, (size_t)T.blk[p].ntet * nc));
       seg.room(p, T.blk[p].nown + 3 * (size_t)T.blk[p].nw);
@@ -389,6 +391,7 @@ void persist_build(int nV, int nT, const int* tets, const std::vector<int>& inc,
   T.loc_v.d[T.loc_v.n++] = 0;   // a block without vertices reads its first one
   tet_e.close(T.tet_e);
   tet_l.close(T.tet_l);
+  return true;
 }
 
 }  // namespace pncg
